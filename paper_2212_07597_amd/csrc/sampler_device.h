@@ -34,12 +34,16 @@ enum { C_PY = 0, C_NAT, C_GN, C_SN, C_GB, C_SB, C_CS, C_CE, C_PT, C_NT, C_LM, C_
 // sample; every other entry ends at one exit offset (CONST; TOTAL when the
 // interval is empty) or depends on the entry (SIM: follow the records).
 enum { MAP_SIM = 0, MAP_CONST = 1, MAP_TOTAL = 2 };
+// Bits of SP_FLG above the kind: copy or timer events present; a SIM
+// segment's kept prefixes are 32-bit values (all inside (-KEPT32, KEPT32)).
+constexpr int FLG_AUX = 4, FLG_FIT = 8;
+constexpr int64_t KEPT32 = (int64_t)1 << 30;
 
 // Per-segment values, one int64 plane each (plane p of segment j at
 // seg[p * nseg + j]), written once per run by the pass named.
 enum {
     // summary pass: sums, extremes of the relative prefixes, chain map (SP_FLG: kind in bits 0-1,
-    // bit 2 = copy or timer events present), and the chain after the first forced sample, which is
+    // FLG_* above), and the chain after the first forced sample, which is
     // the same for every entry: its node (-1 if none), samples after it, best growth sample after
     // it (value, node or -1), largest sampled footprint after it, last sample node after it (or -1)
     // and the Python footprint there (relative values), the forced window's sample mask after it,
@@ -289,6 +293,24 @@ __device__ __forceinline__ void wave_incl_sum3(int64_t& a, int64_t& b, int64_t& 
     b = (int64_t)(((uint64_t)bhi << 32) | blo);
     c = (int64_t)(((uint64_t)chi << 32) | clo);
 }
+// 32-bit inclusive max / min scan (steps as in wave_scan).
+template <bool MAX>
+__device__ __forceinline__ int32_t wave_incl_ext32(int32_t x) {
+    const int32_t id = MAX ? INT32_MIN : INT32_MAX;
+#define INCL32_STEP(CTRL, ROWS)                                                           \
+    {                                                                                     \
+        const int32_t y = __builtin_amdgcn_update_dpp(id, x, CTRL, ROWS, 0xf, false);     \
+        x = MAX ? (x > y ? x : y) : (x < y ? x : y);                                      \
+    }
+    INCL32_STEP(0x111, 0xf)
+    INCL32_STEP(0x112, 0xf)
+    INCL32_STEP(0x114, 0xf)
+    INCL32_STEP(0x118, 0xf)
+    INCL32_STEP(0x142, 0xa)
+    INCL32_STEP(0x143, 0xc)
+#undef INCL32_STEP
+    return x;
+}
 __device__ __forceinline__ int64_t wave_incl_max(int64_t x) { return wave_scan<OpMax>(x); }
 __device__ __forceinline__ int64_t wave_incl_min(int64_t x) { return wave_scan<OpMin>(x); }
 
@@ -309,6 +331,10 @@ __device__ __forceinline__ int32_t wave_ext32(int32_t x) {
     EXT32_STEP(0x143, 0xc)
 #undef EXT32_STEP
     return __builtin_amdgcn_readlane(x, 63);
+}
+
+__device__ __forceinline__ int32_t wave_shr1_32(int32_t x, int32_t old) {
+    return __builtin_amdgcn_update_dpp(old, x, 0x138, 0xf, 0xf, false);
 }
 
 // value of the previous lane (lane 0 gets `old`)

@@ -714,11 +714,29 @@ __device__ bool scan_last_sample(const StatusView& sv, int64_t g, int64_t& oP, u
 // sample area (written only later, by the emit pass): segment j at
 // samples + 4 KB * j.  A trace of fewer than 127 events has too small an
 // area; the resolve pass then scans such segments from their records.
+// A segment whose prefixes all lie in (-2^30, 2^30) keeps them as 32-bit
+// values (flag FLG_FIT): lane l's eight windows side by side, so that a
+// segment is two 16-byte words per lane each way, half the bytes of the
+// 64-bit form (window by window) that the others keep.
 __device__ __forceinline__ bool prefixes_kept(const Desc& D) {
     return (D.n + 1) * sizeof(Sample) >= (uint64_t)D.nseg * SEG * sizeof(int64_t);
 }
 __device__ __forceinline__ SMP_GLOBAL int64_t* kept_prefixes(const Desc& D, int64_t j) {
     return gp((int64_t*)D.samples) + j * SEG;
+}
+
+typedef int32_t v4i32 __attribute__((ext_vector_type(4)));
+
+// The 32-bit kept prefixes of segment j into registers, f[w] = node 64w + l
+// (the loads are issued here; the first use of f waits for them).
+__device__ __forceinline__ void load_kept32(const Desc& D, int64_t j, int32_t (&f)[NW]) {
+    const SMP_GLOBAL v4i32* p = (const SMP_GLOBAL v4i32*)kept_prefixes(D, j) + 2 * lane_id();
+    const v4i32 a = p[0], b = p[1];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        f[w] = a[w];
+        f[4 + w] = b[w];
+    }
 }
 
 __device__ __forceinline__ void summarize_segment(const Desc& D, uint64_t g, int64_t* lF_) {
@@ -806,6 +824,7 @@ __device__ __forceinline__ void summarize_segment(const Desc& D, uint64_t g, int
     sc.any_aux = aux_m != 0;
     sc.err = bad_m ? 1u : 0u;
     SegMap m;
+    int fit = 0;
     if (fnode >= 0) {
         m.lo = 1;
         m.hi = 0;
@@ -815,9 +834,22 @@ __device__ __forceinline__ void summarize_segment(const Desc& D, uint64_t g, int
     } else {
         m = analyse_segment(lF_, T, cF, (int)D.chain_cap);
         if (m.kind == MAP_SIM && prefixes_kept(D)) {
-            SMP_GLOBAL int64_t* o = kept_prefixes(D, j);
+            if (sgt64(KEPT32, sc.mxF) && sgt64(sc.mnF, -KEPT32)) {
+                fit = FLG_FIT;
+                v4i32 a, b;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) o[w * 64 + l] = lF_[w * 64 + l];
+                for (int w = 0; w < 4; ++w) {
+                    a[w] = (int32_t)lF_[w * 64 + l];
+                    b[w] = (int32_t)lF_[(4 + w) * 64 + l];
+                }
+                SMP_GLOBAL v4i32* o = (SMP_GLOBAL v4i32*)kept_prefixes(D, j) + 2 * l;
+                o[0] = a;
+                o[1] = b;
+            } else {
+                SMP_GLOBAL int64_t* o = kept_prefixes(D, j);
+#pragma unroll
+                for (int w = 0; w < NW; ++w) o[w * 64 + l] = lF_[w * 64 + l];
+            }
         }
     }
     const int64_t acnt = r.cnt;
@@ -834,7 +866,7 @@ __device__ __forceinline__ void summarize_segment(const Desc& D, uint64_t g, int
     v = writelane64<SP_LO>(v, m.lo);
     v = writelane64<SP_HI>(v, m.hi);
     v = writelane64<SP_KF>(v, m.kf);
-    v = writelane64<SP_FLG>(v, m.kind | (sc.any_aux ? 4 : 0));
+    v = writelane64<SP_FLG>(v, m.kind | (sc.any_aux ? FLG_AUX : 0) | fit);
     v = writelane64<SP_FN>(v, m.fnode);
     v = writelane64<SP_ACNT>(v, acnt);
     v = writelane64<SP_AGV>(v, r.gbest);
@@ -898,15 +930,27 @@ __device__ __forceinline__ void prescan_segment(const Desc& D, int64_t j, int64_
     }
 }
 
-// The kept prefixes of segment j into F (one wave, one round trip).
-__device__ __forceinline__ void copy_prefixes(const Desc& D, int64_t j, int64_t* F) {
+// The kept prefixes of segment j (fit: in 32 bits) into registers (one round trip).
+__device__ __forceinline__ void load_kept(const Desc& D, int64_t j, bool fit, int64_t (&f)[NW]) {
     const int l = lane_id();
-    const SMP_GLOBAL int64_t* src = kept_prefixes(D, j);
+    if (fit) {
+        int32_t v[NW];
+        load_kept32(D, j, v);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) f[w] = v[w];
+    } else {
+        const SMP_GLOBAL int64_t* F = kept_prefixes(D, j);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) f[w] = F[w * 64 + l];
+    }
+}
+
+// The same into F (one wave).
+__device__ __forceinline__ void copy_prefixes(const Desc& D, int64_t j, bool fit, int64_t* F) {
     int64_t v[NW];
+    load_kept(D, j, fit, v);
 #pragma unroll
-    for (int w = 0; w < NW; ++w) v[w] = src[w * 64 + l];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) F[w * 64 + l] = v[w];
+    for (int w = 0; w < NW; ++w) F[w * 64 + lane_id()] = v[w];
 }
 
 // Exit offset of a segment from entry offset x, following its prefixes F
@@ -929,14 +973,21 @@ __device__ __forceinline__ int64_t walk_prefixes(const int64_t* F, int64_t T, in
     return cr.ref - fend;
 }
 
-// The kept prefixes of segment j into registers (the loads are issued here;
-// the first use of f waits for them).
-__device__ __forceinline__ void load_kept(const Desc& D, int64_t j, int64_t (&f)[NW]) {
-    const int l = lane_id();
-    const SMP_GLOBAL int64_t* F = kept_prefixes(D, j);
-#pragma unroll
-    for (int w = 0; w < NW; ++w) f[w] = F[w * 64 + l];
+// The ends of the 32-bit range stand for anything beyond it: no kept 32-bit
+// prefix reaches them.
+// (compares of 32-bit words: a wave-uniform x stays in scalar registers)
+__device__ __forceinline__ int32_t clamp32(int64_t x) {
+    const int32_t lo = (int32_t)(uint32_t)(uint64_t)x, hi = (int32_t)((uint64_t)x >> 32);
+    return hi == (lo >> 31) ? lo : (hi < 0 ? INT32_MIN : INT32_MAX);
 }
+__device__ __forceinline__ int64_t rl(int64_t v, int l) { return readlane64(v, l); }
+__device__ __forceinline__ int64_t rl(int32_t v, int l) { return (int64_t)readlane32(v, l); }
+template <class FT>
+__device__ __forceinline__ FT threshold_of(int64_t x);
+template <>
+__device__ __forceinline__ int64_t threshold_of<int64_t>(int64_t x) { return x; }
+template <>
+__device__ __forceinline__ int32_t threshold_of<int32_t>(int64_t x) { return clamp32(x); }
 
 // Exit offset from entry offset x, following prefixes held in registers.
 __device__ __forceinline__ int64_t walk_regs(const int64_t (&f)[NW], int64_t T, int64_t x) {
@@ -952,28 +1003,29 @@ __device__ __forceinline__ int64_t walk_regs(const int64_t (&f)[NW], int64_t T, 
 // chain samples once, at the first node at least T above x (x below the
 // interval) or at least T below it (above), and never again in the segment.
 // The eight windows are tested at once, not one after another.
-__device__ __forceinline__ int64_t exit_one_sample(const int64_t (&f)[NW], int64_t T, int64_t x, bool up) {
+template <class FT>
+__device__ __forceinline__ int64_t exit_one_sample(const FT (&f)[NW], int64_t T, int64_t x, bool up) {
     uint64_t m[NW];
     if (up) {  // (wave-uniform: one set of compares, not both and a select)
-        const int64_t thr = x + T;
+        const FT thr = threshold_of<FT>(x + T);
 #pragma unroll
         for (int w = 0; w < NW; ++w) m[w] = ballot(f[w] >= thr);
     } else {
-        const int64_t thr = x - T;
+        const FT thr = threshold_of<FT>(x - T);
 #pragma unroll
         for (int w = 0; w < NW; ++w) m[w] = ballot(f[w] <= thr);
     }
     int64_t fu = x;  // (unreachable for a stop: some node crosses)
 #pragma unroll
     for (int w = NW - 1; w >= 0; --w)
-        if (m[w]) fu = readlane64(f[w], ctz64(m[w]));
-    return fu - readlane64(f[NW - 1], 63);
+        if (m[w]) fu = rl(f[w], ctz64(m[w]));
+    return fu - rl(f[NW - 1], 63);
 }
 
-// The same from the kept prefixes in HBM (all windows loaded at once).
-__device__ __forceinline__ int64_t walk_kept(const Desc& D, int64_t j, int64_t T, int64_t x) {
+// The exit from the kept prefixes in HBM (all windows loaded at once).
+__device__ __forceinline__ int64_t walk_kept(const Desc& D, int64_t j, bool fit, int64_t T, int64_t x) {
     int64_t f[NW];
-    load_kept(D, j, f);
+    load_kept(D, j, fit, f);
     return walk_regs(f, T, x);
 }
 
@@ -1208,13 +1260,14 @@ __global__ __launch_bounds__(64) void k_tmap(const Desc* __restrict__ desc, int 
     const SMP_GLOBAL int64_t* sp = gp(D.seg) + k * TILE;
     // every segment SIM, with a no-sample interval of at least T entries
     // (then max - min < T over its prefixes and the entry)
-    bool ok = prefixes_kept(D);
+    bool ok = prefixes_kept(D), fit = true;  // fit: every segment keeps 32-bit prefixes
     for (int g = 0; g < nval && ok; g += 64) {
         const int s = g + l;
         const bool v = s < nval;
         const int64_t lo = v ? sp[SP_LO * ns + s] : 0, hi = v ? sp[SP_HI * ns + s] : 0;
         const int64_t fl_ = v ? sp[SP_FLG * ns + s] : 0;
         if (ballot(v && ((fl_ & 3) != MAP_SIM || hi < lo || hi - lo < T - 1))) ok = false;
+        if (ballot(v && !(fl_ & FLG_FIT))) fit = false;
     }
     for (int i = l; i < SEG; i += 64) claim[i] = 0;
     int nch = 0, nsrc = 0;
@@ -1390,14 +1443,22 @@ __global__ __launch_bounds__(64) void k_tmap(const Desc* __restrict__ desc, int 
     // copied out at the start of each step: the only loads then in flight
     // are the ones the copy needs, issued a whole step earlier)
     const int64_t j0 = k * TILE;
-    int64_t fn[NW];
-    if (!fail) load_kept(D, j0, fn);
-    for (int s = 0; s < nval && !fail; ++s) {
-        int64_t f[NW];
+    if (fit) {
+        int32_t fn[NW];
+        if (!fail) load_kept32(D, j0, fn);
+        for (int s = 0; s < nval && !fail; ++s) {
+            int64_t f[NW];
 #pragma unroll
-        for (int w = 0; w < NW; ++w) f[w] = fn[w];
-        load_kept(D, j0 + (s + 1 < nval ? s + 1 : s), fn);
-        step(s, f);
+            for (int w = 0; w < NW; ++w) f[w] = fn[w];
+            load_kept32(D, j0 + (s + 1 < nval ? s + 1 : s), fn);
+            step(s, f);
+        }
+    } else {  // (a segment that moves 2^30 or more: loaded as it is used)
+        for (int s = 0; s < nval && !fail; ++s) {
+            int64_t f[NW];
+            load_kept(D, j0 + s, (sp[SP_FLG * ns + s] & FLG_FIT) != 0, f);
+            step(s, f);
+        }
     }
     // runs: consecutive sources of one side that end at the same reference
     int nup = 0, ndn = 0;
@@ -1473,6 +1534,513 @@ __global__ __launch_bounds__(64) void k_tmap(const Desc* __restrict__ desc, int 
     }
 }
 
+// ------------------------------------------------------------ block maps
+//
+// The chain map of a block of 64 consecutive segments over all entry offsets
+// (section 3.2, by the steps of the tile maps above, but for segments of any
+// map kind that may sample several times): one wave follows the block's
+// distinct chains segment by segment, the 8 waves of a tile at once, so that
+// a tile costs the time of 64 segments instead of 512 and its entry is needed
+// only for eight lookups.  Chains live in lanes (two per lane); a chain is
+// named by the source that started it, and a chain that reaches a node where
+// another has sampled ends there and points to that one.  Every chain's
+// reference after every segment is written to the sample area, so that the
+// exits of all segments follow from the block's entry by reading one column
+// per stretch of the entry's path.
+//
+// Coordinates are footprints relative to the block start, as 32-bit values:
+// T and all of them must stay below 2^30 in magnitude, the SIM segments must
+// keep 32-bit prefixes, and the block's entries must all have sampled within
+// its first BM_OPEN segments (a threshold far above what a segment moves
+// would start more chains than fit); a tile that does not qualify, or whose
+// blocks start more, is walked instead.
+// Bound: the serial chain of one wave through 64 segments (a sample of a lone
+// chain costs ~250 ns of dependent ballots and LDS reads; the first samples of
+// many chains are searched side by side).  Measured, resolve pass: 1,024
+// traces of 1e3-1e6 events at T = 256 KiB / 1 MiB / 10 MiB 1.12 -> 0.32 ms; a
+// trace of 777,777 events at T = 3 MiB (three tiles) 1.53 -> 0.17 ms; one of
+// 1.2e7 events at T = 10 MiB 9.5 -> 0.2 ms.  A tile of few SIM segments
+// (below BM_MIN_SIM) walks them in less time than a block map takes.
+constexpr int BM_SRC = 512;   // sources per block
+constexpr int BM_OPEN = 14;   // ~31 sources per segment on the log-uniform mixes while entries are left
+constexpr int BM_MIN_SIM = 8; // SIM segments of a tile below which the walk is short anyway
+constexpr int BM_PAR = 4;     // chains that stop in a segment from which they are searched side by side
+
+struct alignas(16) BlockLds {
+    int32_t f[SEG];          // the current SIM segment's prefixes
+    int32_t sb[BM_SRC];      // source bounds (entry offsets at the block start): 2 * bound, + 1 for a source of the
+                             // entries below the unsampled interval (its largest; + 0: above, its smallest)
+    int32_t ex[128];         // exit offset of each column's chain
+    uint16_t claim[SEG];     // chain that sampled at each node: (segment + 1) << 9 | chain
+    uint16_t init[BM_SRC];   // the chain the source joins
+    uint16_t par[BM_SRC];    // chain a chain has merged into (itself: none)
+    uint8_t cseg[BM_SRC];    // the segment where the source joins it
+    uint8_t mseg[BM_SRC];    // the segment where the chain merged
+    uint8_t slot[BM_SRC];    // a chain's column
+};
+constexpr uint32_t BM_ID = BM_SRC - 1;
+static_assert(BM_SRC == 1 << 9, "a claim holds the segment and the chain");
+// value pushed to lane dst (lanes that none is pushed to receive 0)
+__device__ __forceinline__ int32_t push32(int32_t v, int dst) { return __builtin_amdgcn_ds_permute(dst << 2, v); }
+
+// The references after each segment: 128 columns of 32-bit values per
+// segment, in the sample area behind the kept prefixes.
+__device__ __forceinline__ bool block_rows_fit(const Desc& D) {
+    return (D.n + 1) * sizeof(Sample) >= (uint64_t)D.nseg * (SEG * sizeof(int64_t) + 512);
+}
+__device__ __forceinline__ SMP_GLOBAL int32_t* block_row(const Desc& D, int64_t j) {
+    return (SMP_GLOBAL int32_t*)((SMP_GLOBAL uint8_t*)gp((uint8_t*)D.samples) + (uint64_t)D.nseg * (SEG * 8) +
+                                 (uint64_t)j * 512);
+}
+
+// A block's map as the wave that built it holds it (uniform values, but for
+// ref: lane i's is the one reference after segment i, from segment one_from on).
+struct BlockMap {
+    int ok;
+    int nsrc;
+    int32_t umax, umin;  // unsampled entries: [umax - T + 1, umin + T - 1]
+    int32_t rend;        // the block's footprint change
+    int one_from;        // from this segment's end on every entry has one reference (64: never)
+    int32_t ref;
+};
+
+// The next sample of a chain in a segment whose prefixes lie in f and whose
+// eight-node groups (lane g: nodes 8g .. 8g + 7) reach from gn to gx: one
+// ballot over the groups, one over the nodes of the first group that crosses.
+// The search goes on from node 8 * gfrom + efrom; a crossing group whose
+// crossings all lie before it is passed over.
+struct NextSample {
+    int node;     // SEG: none
+    int32_t f;
+    uint32_t claim;
+};
+__device__ __forceinline__ NextSample next_sample(const BlockLds& B, int32_t gx, int32_t gn, int32_t T, int32_t xr,
+                                                  int from) {
+    const int l = lane_id();
+    const uint32_t span = (uint32_t)(2 * T - 1);
+    NextSample r{SEG, 0, 0};
+    uint64_t gm = from < SEG ? ballot(gx >= xr + T || gn <= xr - T) & (~0ull << (from >> 3)) : 0;
+    while (gm) {
+        const int g = ctz64(gm);
+        const int32_t v = B.f[8 * g + (l & 7)];
+        const uint32_t c = B.claim[8 * g + (l & 7)];
+        uint64_t m = ballot((uint32_t)(v + (T - 1) - xr) >= span) & 0xFFull;
+        if (8 * g < from) m &= ~0ull << (from & 7);
+        if (m) {
+            const int j = ctz64(m);
+            r.node = 8 * g + j;
+            r.f = readlane32(v, j);
+            r.claim = (uint32_t)readlane32((int)c, j);
+            break;
+        }
+        gm &= gm - 1;
+    }
+    return r;
+}
+
+// Build the map of the block at segment j0 of nb segments; lane i holds
+// segment i's kind, offset Rv, extremes Sxv, Snv and constant exit kxv (block
+// coordinates).
+__device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int nb, int32_t T, int kindv, int32_t Rv,
+                                                int32_t Sxv, int32_t Snv, int32_t kxv, int32_t rend, BlockLds& B) {
+    const int l = lane_id();
+    int32_t XA = 0, XB = 0;     // lane l: chains in columns l and 64 + l
+    int idA = 0, idB = 0;
+    uint64_t alA = 0, alB = 0;  // columns in use
+    int nsrc = 0;
+    int32_t Umax = 0, Umin = 0;
+    bool open = true, ok = true;
+    const uint64_t simm = ballot(l < nb && kindv == MAP_SIM);
+    for (int i = l; i < SEG; i += 64) B.claim[i] = 0;
+    // the next SIM segment's prefixes load while one is processed
+    int32_t pf[NW];
+    auto prefetch = [&](int s) {
+        const uint64_t m = s < 64 ? simm & (~0ull << s) : 0;
+        load_kept32(D, j0 + (m ? ctz64(m) : 0), pf);
+    };
+    // segment s's prefixes (just prefetched) into LDS, and their group extremes
+    int32_t gx = 0, gn = 0;
+    auto take = [&](int s) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) B.f[w * 64 + l] = pf[w];
+        prefetch(s + 1);
+        const v4i32 a = *(const v4i32*)&B.f[8 * l], b = *(const v4i32*)&B.f[8 * l + 4];
+        gx = a[0];
+        gn = a[0];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            gx = a[i] > gx ? a[i] : gx;
+            gx = b[i] > gx ? b[i] : gx;
+            gn = a[i] < gn ? a[i] : gn;
+            gn = b[i] < gn ? b[i] : gn;
+        }
+    };
+    // Follow chain id from reference xr (relative to segment s) from node st
+    // on; the chain it meets, or -1 at the segment end.  (A segment that
+    // moves less than T holds one sample of a chain.)
+    auto follow = [&](int32_t& xr, int st, int id, int s, bool single) -> int {
+        for (;;) {
+            const NextSample n = next_sample(B, gx, gn, T, xr, st);
+            if (n.node >= SEG) return -1;
+            if ((n.claim >> 9) == (uint32_t)(s + 1)) return (int)(n.claim & BM_ID);
+            B.claim[n.node] = (uint16_t)((s + 1) << 9 | id);
+            xr = n.f;
+            st = n.node + 1;
+            if (single) return -1;
+        }
+    };
+    // Columns for the new chains of the lanes in nm (reference X, name id).
+    auto new_columns = [&](uint64_t nm, int32_t X, int id) {
+        const int n = __popcll(nm), na = __popcll(~alA);
+        if (n > na + __popcll(~alB)) {
+            ok = false;
+            return;
+        }
+        const int rank = __popcll(nm & lanemask_lt());
+        // the chains in rank order, one per lane (lanes outside nm push past them)
+        const bool mine = (nm >> l) & 1;
+        const int dst = mine ? rank : n + (l - rank);
+        const int32_t px = push32(X, dst), pid = push32(id, dst);
+        const int ra = __popcll(~alA & lanemask_lt()), rb = na + __popcll(~alB & lanemask_lt());
+        const bool ta = !((alA >> l) & 1) && ra < n, tb = !((alB >> l) & 1) && rb < n;
+        const int32_t xa = shfl32(px, ra & 63), ia = shfl32(pid, ra & 63);
+        XA = ta ? xa : XA;
+        idA = ta ? ia : idA;
+        if (ta) B.slot[ia] = (uint8_t)l;
+        alA |= ballot(ta);
+        if (n > na) {
+            const int32_t xb = shfl32(px, rb & 63), ib = shfl32(pid, rb & 63);
+            XB = tb ? xb : XB;
+            idB = tb ? ib : idB;
+            if (tb) B.slot[ib] = (uint8_t)(64 + l);
+            alB |= ballot(tb);
+        }
+    };
+    // The stopping chains st of one group of columns through the segment in
+    // B.f: their first samples side by side (a search over the running
+    // extremes of the groups, then over the eight nodes of one), the ones at
+    // one node merged, the rest of the segment one chain after another.
+    auto stop_group = [&](uint64_t& al, uint64_t st, int32_t& X, int id, int32_t R, int s, bool single, int32_t cgx,
+                          int32_t cgn) {
+        const uint32_t span = (uint32_t)(2 * T - 1);
+        const bool mine = (st >> l) & 1;
+        const int32_t xr = mine ? X - R : 0;
+        const int32_t hi = xr + T, lo = xr - T;
+        int g = 0;
+#pragma unroll
+        for (int d = 32; d; d >>= 1) {
+            const int32_t x = shfl32(cgx, g + d - 1), n = shfl32(cgn, g + d - 1);
+            g += x >= hi || n <= lo ? 0 : d;
+        }
+        g &= 63;  // (a stopping chain crosses in some group)
+        const v4i32 a = *(const v4i32*)&B.f[8 * g], b = *(const v4i32*)&B.f[8 * g + 4];
+        int e = 7;
+        int32_t v = b[3];
+#pragma unroll
+        for (int i = 6; i >= 0; --i) {
+            const int32_t y = i < 4 ? a[i & 3] : b[i & 3];
+            const bool c = (uint32_t)(y + (T - 1) - xr) >= span;
+            e = c ? i : e;
+            v = c ? y : v;
+        }
+        const int node = 8 * g + e;
+        const uint32_t tag = (uint32_t)(s + 1) << 9, key = tag | (uint32_t)id;
+        uint32_t got = mine ? B.claim[node] : 0;
+        const bool taken = (got >> 9) == (uint32_t)(s + 1);
+        if (mine && !taken) B.claim[node] = (uint16_t)key;
+        asm volatile("" ::: "memory");  // (several lanes may write one claim: what it holds is read back)
+        if (mine && !taken) got = B.claim[node];
+        const bool win = mine && got == key;
+        if (mine && !win) {
+            B.par[id] = (uint16_t)(got & BM_ID);
+            B.mseg[id] = (uint8_t)s;
+        }
+        const uint64_t wm = ballot(win);
+        al = (al & ~st) | wm;
+        X = win ? R + v : X;
+        if (single) return;
+        for (uint64_t m = wm; m; m &= m - 1) {
+            const int c = ctz64(m), cid = readlane32(id, c);
+            int32_t x = readlane32(v, c);
+            const int to = follow(x, readlane32(node, c) + 1, cid, s, false);
+            if (to >= 0) {
+                B.par[cid] = (uint16_t)to;
+                B.mseg[cid] = (uint8_t)s;
+                al &= ~(1ull << c);
+            }
+            X = l == c ? R + x : X;
+        }
+    };
+    // The same, one chain after another.
+    auto stop_each = [&](uint64_t& al, uint64_t st, int32_t& X, int id, int32_t R, int s, bool single) {
+        for (uint64_t m = st; m; m &= m - 1) {
+            const int c = ctz64(m), cid = readlane32(id, c);
+            int32_t x = readlane32(X, c) - R;
+            const int to = follow(x, 0, cid, s, single);
+            if (to >= 0) {
+                B.par[cid] = (uint16_t)to;
+                B.mseg[cid] = (uint8_t)s;
+                al &= ~(1ull << c);
+            }
+            X = l == c ? R + x : X;
+        }
+    };
+    prefetch(0);
+    int s = 0;
+    // every chain, until one is left and no entry is unsampled
+    for (; s < nb && ok; ++s) {
+        if (!open && __popcll(alA) + __popcll(alB) == 1) break;
+        const int kind = readlane32(kindv, s);
+        const int32_t R = readlane32(Rv, s), Sx = readlane32(Sxv, s), Sn = readlane32(Snv, s);
+        uint64_t stA = alA & ballot(XA <= Sx - T || XA >= Sn + T), stB = alB & ballot(XB <= Sx - T || XB >= Sn + T);
+        bool fresh = open && (Sx > Umax || Sn < Umin);
+        if (kind == MAP_TOTAL) {
+            stA = alA;
+            stB = alB;
+            fresh = open;
+        }
+        if (kind != MAP_SIM) {
+            if (stA | stB | (fresh ? 1ull : 0ull)) {
+                // every chain and entry that samples leaves at one reference:
+                // the first source's new chain, or the first chain's
+                const int32_t kx = readlane32(kxv, s);
+                int id = nsrc;
+                if (stA) id = readlane32(idA, ctz64(stA));
+                else if (stB) id = readlane32(idB, ctz64(stB));
+                if (fresh) {
+                    const int32_t mx = Sx > Umax ? Sx : Umax, uhi = Umin + T - 1;
+                    const bool all = kind == MAP_TOTAL;
+                    const bool up = all || Sx > Umax;
+                    const bool dn = !all && Sn < Umin && mx - Umin <= 2 * T - 2;
+                    const int add = (up ? 1 : 0) + (dn ? 1 : 0);
+                    if (nsrc + add > BM_SRC) {
+                        ok = false;
+                        break;
+                    }
+                    if (l < add) {
+                        const bool u = up && l == 0;
+                        const int src = nsrc + l;
+                        B.sb[src] = u ? 2 * (all || uhi < Sx - T ? uhi : Sx - T) + 1
+                                      : 2 * (mx - T + 1 > Sn + T ? mx - T + 1 : Sn + T);
+                        B.init[src] = (uint16_t)id;
+                        B.cseg[src] = (uint8_t)s;
+                        B.par[src] = (uint16_t)id;
+                        B.mseg[src] = (uint8_t)s;
+                    }
+                    if (!(stA | stB)) new_columns(1ull, kx, id);
+                    nsrc += add;
+                }
+                // the others end in it
+                if (((stA >> l) & 1) && idA != id) {
+                    B.par[idA] = (uint16_t)id;
+                    B.mseg[idA] = (uint8_t)s;
+                }
+                if (((stB >> l) & 1) && idB != id) {
+                    B.par[idB] = (uint16_t)id;
+                    B.mseg[idB] = (uint8_t)s;
+                }
+                if (stA) {
+                    const uint64_t first = stA & (~stA + 1);
+                    alA = (alA & ~stA) | first;
+                    alB &= ~stB;
+                    XA = (first >> l) & 1 ? kx : XA;
+                } else if (stB) {
+                    const uint64_t first = stB & (~stB + 1);
+                    alB = (alB & ~stB) | first;
+                    XB = (first >> l) & 1 ? kx : XB;
+                }
+            }
+        } else if (stA | stB | (fresh ? 1ull : 0ull)) {
+            take(s);
+            const bool single = Sx - Sn < T;
+            if (__popcll(stA) + __popcll(stB) >= BM_PAR) {
+                const int32_t cgx = wave_incl_ext32<true>(gx), cgn = wave_incl_ext32<false>(gn);
+                if (stA) stop_group(alA, stA, XA, idA, R, s, single, cgx, cgn);
+                if (stB) stop_group(alB, stB, XB, idB, R, s, single, cgx, cgn);
+            } else {
+                stop_each(alA, stA, XA, idA, R, s, single);
+                stop_each(alB, stB, XB, idB, R, s, single);
+            }
+            if (fresh) {
+                // nodes beyond the extremes so far: first samples of unsampled entries
+                int32_t cm = Umax, cn = Umin;
+                for (int w = 0; w < NW && ok && cm - cn <= 2 * T - 2; ++w) {
+                    const int32_t fv = B.f[w * 64 + l], gv = R + fv;
+                    if (!ballot(gv > cm || gv < cn)) continue;
+                    int32_t im = wave_incl_ext32<true>(gv), in = wave_incl_ext32<false>(gv);
+                    im = im > cm ? im : cm;
+                    in = in < cn ? in : cn;
+                    const int32_t pm = wave_shr1_32(im, cm), pn = wave_shr1_32(in, cn);  // before the node
+                    const bool op = pm - pn <= 2 * T - 2;
+                    const bool up = op && gv > pm, dn = op && gv < pn;
+                    const uint64_t spm = ballot(up || dn);
+                    cm = readlane32(im, 63);
+                    cn = readlane32(in, 63);
+                    if (nsrc + __popcll(spm) > BM_SRC) {
+                        ok = false;
+                        break;
+                    }
+                    // the sources, in node order; each starts a chain at its
+                    // node or joins the one that sampled there
+                    const bool mine = (spm >> l) & 1;
+                    const int src = nsrc + __popcll(spm & lanemask_lt());
+                    if (mine) {
+                        B.sb[src] = up ? 2 * (pn + T - 1 < gv - T ? pn + T - 1 : gv - T) + 1
+                                       : 2 * (pm - T + 1 > gv + T ? pm - T + 1 : gv + T);
+                        B.cseg[src] = (uint8_t)s;
+                        B.par[src] = (uint16_t)src;
+                    }
+                    if (single) {  // (no chain samples again: all at once)
+                        const uint32_t cl = mine ? B.claim[w * 64 + l] : 0;
+                        const bool hit = (cl >> 9) == (uint32_t)(s + 1);
+                        if (mine) {
+                            B.init[src] = (uint16_t)(hit ? (int)(cl & BM_ID) : src);
+                            if (!hit) B.claim[w * 64 + l] = (uint16_t)((s + 1) << 9 | src);
+                        }
+                        new_columns(spm & ~ballot(hit), gv, src);
+                        nsrc += __popcll(spm);
+                        continue;
+                    }
+                    for (uint64_t m = spm; m && ok; m &= m - 1) {
+                        const int c = ctz64(m), sc = nsrc++;
+                        const uint32_t cl = (uint32_t)__builtin_amdgcn_readfirstlane((int)B.claim[w * 64 + c]);
+                        if ((cl >> 9) == (uint32_t)(s + 1)) {
+                            B.init[sc] = (uint16_t)(cl & BM_ID);
+                            continue;
+                        }
+                        B.claim[w * 64 + c] = (uint16_t)((s + 1) << 9 | sc);
+                        B.init[sc] = (uint16_t)sc;
+                        int32_t xr = readlane32(fv, c);
+                        const int to = follow(xr, w * 64 + c + 1, sc, s, false);
+                        if (to >= 0) {
+                            B.par[sc] = (uint16_t)to;
+                            B.mseg[sc] = (uint8_t)s;
+                        } else {
+                            new_columns(1ull, R + xr, sc);
+                        }
+                    }
+                }
+            }
+        } else {
+            prefetch(s + 1);
+        }
+        Umax = Sx > Umax ? Sx : Umax;
+        Umin = Sn < Umin ? Sn : Umin;
+        open = open && kind != MAP_TOTAL && Umax - Umin <= 2 * T - 2;
+        SMP_GLOBAL int32_t* row = block_row(D, j0 + s);
+        row[l] = XA;
+        if (alB) row[64 + l] = XB;
+    }
+    BlockMap r{ok ? 1 : 0, nsrc, Umax, Umin, rend, 64, 0};
+    if (!ok) return r;
+    if (!open) {  // (a closed interval stays closed whatever the extremes do later)
+        r.umax = T;
+        r.umin = -T;
+    }
+    if (!open && __popcll(alA) + __popcll(alB) == 1) {
+        // One reference is left: followed alone to the block end, all
+        // segments up to its next stop at once, and a run of segments that
+        // each take their predecessor's one exit to their own at once too.
+        r.one_from = s > 0 ? s - 1 : 0;
+        int32_t X = alA ? readlane32(XA, ctz64(alA)) : readlane32(XB, ctz64(alB));
+        const int32_t kp = wave_shr1_32(kxv, 0);
+        const uint64_t runm =
+            ballot(l > 0 && l < nb && kindv != MAP_SIM && (kindv == MAP_TOTAL || kp <= Sxv - T || kp >= Snv + T));
+        r.ref = X;
+        while (s < nb) {
+            const uint64_t stop =
+                ballot(l >= s && l < nb && (kindv == MAP_TOTAL || X <= Sxv - T || X >= Snv + T));
+            if (l >= s) r.ref = X;
+            if (!stop) break;
+            const int i = ctz64(stop);
+            if ((simm >> i) & 1) {
+                // (the prefetch may hold another segment)
+                const uint64_t m = s < 64 ? simm & (~0ull << s) : 0;
+                if (!m || ctz64(m) != i) prefetch(i);
+                take(i);
+                const int32_t R = readlane32(Rv, i);
+                const bool single = readlane32(Sxv, i) - readlane32(Snv, i) < T;
+                int32_t xr = X - R;
+                for (int st = 0; st < SEG;) {
+                    const NextSample n = next_sample(B, gx, gn, T, xr, st);
+                    if (n.node >= SEG) break;
+                    xr = n.f;
+                    st = single ? SEG : n.node + 1;
+                }
+                X = R + xr;
+                if (l >= i) r.ref = X;
+                s = i + 1;
+            } else {
+                // i and the run after it
+                const uint64_t nr = ~runm & ~(i < 63 ? ((2ull << i) - 1) : ~0ull);
+                const int e = nr ? ctz64(nr) : 64;  // first segment past the run
+                if (l >= i && l < e) r.ref = kxv;
+                X = readlane32(kxv, e - 1);
+                const uint64_t pm = s < 64 ? simm & (~0ull << s) : 0, qm = e < 64 ? simm & (~0ull << e) : 0;
+                if (qm && ctz64(qm) != (pm ? ctz64(pm) : 64)) prefetch(e);
+                s = e;
+            }
+        }
+        B.ex[0] = X - rend;
+        return r;
+    }
+    B.ex[l] = XA - rend;
+    B.ex[64 + l] = XB - rend;
+    return r;
+}
+
+// The source that holds entry e of a block (-1: e has not sampled at the block end).
+__device__ __forceinline__ int block_source(const BlockLds& B, int nsrc, int32_t umax, int32_t umin, int32_t T,
+                                            int32_t e) {
+    const int l = lane_id();
+    if (e >= umax - T + 1 && e <= umin + T - 1) return -1;
+    int dn = -1;
+    for (int g = 0; g < nsrc; g += 64) {
+        const int s = g + l;
+        const bool v = s < nsrc;
+        const int32_t b2 = v ? B.sb[s] : 0, b = b2 >> 1;
+        const bool up = (b2 & 1) != 0;
+        const uint64_t u = ballot(v && up && b >= e), d = ballot(v && !up && b <= e);
+        if (u) return g + ctz64(u);
+        if (d && dn < 0) dn = g + ctz64(d);
+    }
+    return dn;  // (every entry outside the interval has one)
+}
+
+// A block's exit offset of the entries of source src.
+__device__ __forceinline__ int32_t block_exit(const BlockLds& B, const BlockMap& m, int src) {
+    if (m.one_from < 64) return __builtin_amdgcn_readfirstlane(B.ex[0]);
+    int id = readlane32((int)B.init[src], 0);
+    for (int d = 0; d < BM_SRC; ++d) {
+        const int to = readlane32((int)B.par[id], 0);
+        if (to == id) break;
+        id = to;
+    }
+    return __builtin_amdgcn_readfirstlane(B.ex[readlane32((int)B.slot[id], 0)]);
+}
+
+// The reference after each segment of the block (lane i: segment i) of the
+// chain from entry e, whose source is src (one_from, ref: the block's map).
+__device__ __forceinline__ int32_t block_refs(const Desc& D, int64_t j0, int nb, const BlockLds& B, int one_from,
+                                              int32_t ref, int32_t e, int src) {
+    const int l = lane_id();
+    int col = -1;
+    if (src >= 0 && one_from > 0) {
+        int from = readlane32((int)B.cseg[src], 0), id = readlane32((int)B.init[src], 0);
+        for (int d = 0; d < BM_SRC; ++d) {
+            const int to = readlane32((int)B.par[id], 0);
+            const int until = to == id ? 64 : readlane32((int)B.mseg[id], 0);
+            const int sl = readlane32((int)B.slot[id], 0);
+            if (l >= from && l < until) col = sl;
+            if (to == id) break;
+            from = until > from ? until : from;
+            id = to;
+        }
+    }
+    if (l >= one_from) return ref;
+    return col >= 0 && l < nb ? block_row(D, j0 + l)[col] : e;
+}
+
 // One workgroup per tile of TILE segments (tiles taken in ticket order, so a
 // tile's predecessors are always running or done): exclusive prefix sums and
 // the chain's entry and exit offset of every segment.
@@ -1486,7 +2054,8 @@ __global__ __launch_bounds__(64) void k_tmap(const Desc* __restrict__ desc, int 
 // interval.  A SIM segment where it stops is followed through its records;
 // the other waves scan the SIM segments' footprint prefixes into an LDS ring
 // ahead of the walker (skipping those it has already passed), so each one
-// costs the walker only a pass over LDS.
+// costs the walker only a pass over LDS.  Tiles of several SIM segments whose
+// blocks qualify take block maps (above) instead of the walk.
 __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void k_resolve(const Desc* __restrict__ desc, int ntraces, uint64_t ntile_total,
                                                   unsigned long long* ctl) {
     __shared__ unsigned long long s_tk;
@@ -1494,10 +2063,23 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     __shared__ int64_t s_pre[3];
     __shared__ int64_t w_peak[TWAVES], w_peakS[TWAVES];
     __shared__ int w_left[TWAVES];
-    __shared__ int64_t m_lo[TILE], m_hi[TILE], m_af[TILE], m_kf[TILE], m_ex[TILE];
-    __shared__ int64_t m_R[TILE];  // sparse tiles: the footprint change before each segment
+    __shared__ int64_t m_ex[TILE];
     __shared__ uint64_t w_tot[TWAVES], w_sim[TWAVES];  // valid lanes with TOTAL / SIM maps
-    __shared__ int64_t ring[RING][SEG];
+    __shared__ uint64_t w_fit[TWAVES];                 // lanes whose kept prefixes are 32-bit values
+    __shared__ union {
+        struct {
+            int64_t ring[RING][SEG];
+            int64_t lo[TILE], hi[TILE], af[TILE], kf[TILE];
+            int64_t R[TILE];  // sparse tiles: the footprint change before each segment
+        } w;
+        BlockLds blk[TWAVES];  // (a tile uses one or the other)
+    } u_;
+    int64_t (&ring)[RING][SEG] = u_.w.ring;
+    int64_t (&m_lo)[TILE] = u_.w.lo, (&m_hi)[TILE] = u_.w.hi, (&m_af)[TILE] = u_.w.af, (&m_kf)[TILE] = u_.w.kf;
+    int64_t (&m_R)[TILE] = u_.w.R;
+    __shared__ BlockMap s_bm[TWAVES];
+    __shared__ int s_bok[TWAVES], s_bsrc[TWAVES];
+    __shared__ int32_t s_bent[TWAVES + 1];
     __shared__ int r_ready[RING];  // walk-order SIM index held by each slot
     __shared__ int s_prod, s_cons, s_abort;
     __shared__ int w_wide[TWAVES];
@@ -1521,8 +2103,8 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     const int nval = (int)((ns - k * TILE) < TILE ? (ns - k * TILE) : TILE);  // valid lanes
     const StatusView ts{D.tstat, (int64_t)D.ntile};
     const SMP_GLOBAL int64_t* sp = gp(D.seg) + (valid ? j : 0);
-    int64_t af = 0, ap = 0, ac = 0, kf = 0, lo = 0, hi = 0;
-    int kind = MAP_CONST;
+    int64_t af = 0, ap = 0, ac = 0, kf = 0, lo = 0, hi = 0, mxf = 0, mnf = 0;
+    int kind = MAP_CONST, flg = 0;
     if (valid) {
         af = sp[SP_AF * ns];
         ap = sp[SP_AP * ns];
@@ -1530,7 +2112,10 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
         lo = sp[SP_LO * ns];
         hi = sp[SP_HI * ns];
         kf = sp[SP_KF * ns];
-        kind = (int)(sp[SP_FLG * ns] & 3);
+        mxf = sp[SP_MXF * ns];
+        mnf = sp[SP_MNF * ns];
+        flg = (int)sp[SP_FLG * ns];
+        kind = flg & 3;
     }
     m_lo[tid] = lo;
     m_hi[tid] = hi;
@@ -1538,6 +2123,9 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     m_kf[tid] = kf;
     m_ex[tid] = kf;  // final for total maps; the walker overwrites the others
     const uint64_t tot = ballot(valid && kind == MAP_TOTAL), sim = ballot(valid && kind == MAP_SIM);
+    const uint64_t fitm = ballot((flg & FLG_FIT) != 0);
+    const int64_t T = D.T;
+    const bool kept = prefixes_kept(D);
     // sums inside the wave
     int64_t iF = af, iP = ap, iC = ac;
     wave_incl_sum3(iF, iP, iC);
@@ -1551,7 +2139,25 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     if (l == 0) {
         w_tot[wv] = tot;
         w_sim[wv] = sim;
+        w_fit[wv] = fitm;
         w_wide[wv] = nwide_w;
+    }
+    // whether this wave's 64 segments may get a block map (see there)
+    const int nb = nval - wv * 64 < 64 ? nval - wv * 64 : 64;
+    const int64_t bR = iF - af;
+    int32_t bSx = 0, bSn = 0;
+    {
+        const bool in = bR + mxf < KEPT32 && bR + mnf > -KEPT32 && bR + af < KEPT32 && bR + af > -KEPT32 &&
+                        (kind != MAP_SIM || (flg & FLG_FIT));
+        bool q = T < KEPT32 && kept && block_rows_fit(D) && !ballot(valid && !in);
+        if (q) {
+            bSx = (int32_t)(bR + mxf);
+            bSn = (int32_t)(bR + mnf);
+            const int32_t x = wave_ext32<true>(l < BM_OPEN && valid ? bSx : 0);
+            const int32_t n = wave_ext32<false>(l < BM_OPEN && valid ? bSn : 0);
+            q = nb <= BM_OPEN || (int64_t)x - n > 2 * T - 2 || (tot & ((1ull << BM_OPEN) - 1)) != 0;
+        }
+        if (l == 0) s_bok[wv] = q ? 1 : 0;
     }
     __syncthreads();
     int64_t oF = 0, oP = 0, oC = 0, tF = 0, tP = 0, tC = 0;
@@ -1568,6 +2174,9 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
         tP += w_sum[1][w];
         tC += w_sum[2][w];
     }
+    tF = readlane64(tF, 0);  // (wave-uniform: scalar registers)
+    tP = readlane64(tP, 0);
+    tC = readlane64(tC, 0);
     // prefixes relative to the tile start (the tile's own prefix is added at the end)
     const int64_t rF = oF + iF - af, rP = oP + iP - ap, rC = oC + iC - ac;
     // SIM segments in walk order: (ft, nval) first, then [0, ft)
@@ -1580,9 +2189,6 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     // publish the tile's sums (inclusive right away for the first tile)
     if (tid < 3) st_status(ts.at(W_AF + tid, k), pack(tid == 0 ? tF : (tid == 1 ? tP : tC), 1));
     if (k == 0 && tid < 3) st_status(ts.at(W_IF + tid, k), pack(tid == 0 ? tF : (tid == 1 ? tP : tC), 1));
-    const int64_t T = D.T;
-
-    const bool kept = prefixes_kept(D);
     // Sparse tile: most SIM maps leave at least half of the entries without a
     // sample, so the walker stops at few of them (T far above what a segment
     // moves).  Producers pre-scanning every SIM segment would fall behind the
@@ -1590,12 +2196,96 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     // of the walker's own (each stop of the walker waits for one): here the
     // other waves stay idle and the walker reads the kept prefixes itself.
     const bool sparse = kept && nsim > 0 && 4 * nwide >= 3 * nsim;
-    if (sparse) {
-        // the walker reads footprint offsets inside the tile from LDS instead
-        // of scanning each group of 64 segments it enters
-        m_R[tid] = rF;
+    // The tile's prefix sums (one wave).
+    auto tile_sums = [&]() {
+        int64_t pF = 0, pP = 0, pC = 0;
+        bool ok = true;
+        if (k > 0) {
+            ok = scan_sums(ts, k, pF, pP, pC, ctl);
+            if (l < 3) st_status(ts.at(W_IF + l, k), pack(l == 0 ? pF + tF : (l == 1 ? pP + tP : pC + tC), 1));
+        }
+        if (l == 0) {
+            s_pre[0] = pF;
+            s_pre[1] = pP;
+            s_pre[2] = pC;
+            if (!ok) g_or32(&D.scal->err, 8u);
+        }
+    };
+    // Block maps: the tile's eight blocks are followed for all entries at
+    // once, one wave each; the tile's entry then costs eight lookups and the
+    // segments' exits are read from the rows its chain left.
+    bool blocks = nsim >= BM_MIN_SIM;
+    for (int w = 0; w < TWAVES; ++w) blocks = blocks && s_bok[w] != 0;
+    const bool tried = blocks;
+    int32_t bref = 0;  // (BlockMap::ref)
+    if (blocks) {
+        const BlockMap bm = build_block(D, k * TILE + wv * 64, nb, (int32_t)T, kind, (int32_t)bR, bSx, bSn,
+                                        (int32_t)(bR + af + kf), readlane32((int32_t)(bR + af), 63), u_.blk[wv]);
+        bref = bm.ref;
+        if (l == 0) s_bm[wv] = bm;
         __syncthreads();
+        for (int w = 0; w < TWAVES; ++w) blocks = blocks && s_bm[w].ok != 0;
     }
+    if (blocks) {
+        if (wv == 0) {
+            const int32_t t32 = (int32_t)T;
+            auto follow_block = [&](int b, int32_t e) {
+                const BlockMap& m = s_bm[b];
+                const int src = __builtin_amdgcn_readfirstlane(
+                    block_source(u_.blk[b], m.nsrc, m.umax, m.umin, t32, e));
+                s_bsrc[b] = src;
+                return src < 0 ? e - m.rend : block_exit(u_.blk[b], m, src);
+            };
+            // from the last block that every entry leaves at one exit, the
+            // tile's exit does not depend on its entry: published first
+            int c = -1;
+            for (int b = 0; b < TWAVES; ++b)
+                if (s_bm[b].one_from < 64) c = b;
+            bool out = false;
+            if (c >= 0) {
+                int32_t x = __builtin_amdgcn_readfirstlane(u_.blk[c].ex[0]);
+                for (int b = c + 1; b < TWAVES; ++b) x = follow_block(b, x);
+                st_status(ts.at(W_XF, k), pack(x, 1));
+                out = true;
+            }
+            int64_t e = 0;
+            bool ok = true;
+            if (k > 0) ok = wait_word(ts.at(W_XF, k - 1), e, ctl);
+            int32_t x = (int32_t)e;
+            for (int b = 0; b < TWAVES; ++b) {
+                s_bent[b] = x;
+                x = follow_block(b, x);
+            }
+            if (!out && ok) {
+                // a tile map may have published the exit already: it must agree
+                const uint64_t pw = ld_status(ts.at(W_XF, k));
+                if (wstate(pw) && unpack(pw) != x && l == 0) g_or32(&D.scal->err, 4u);
+                st_status(ts.at(W_XF, k), pack(x, 1));
+            }
+            if (l == 0) {
+                s_entry = e;
+                if (!ok) g_or32(&D.scal->err, 8u);
+            }
+        } else if (wv == 1) {
+            tile_sums();
+        }
+        __syncthreads();
+        const int32_t ref = block_refs(D, k * TILE + wv * 64, nb, u_.blk[wv], s_bm[wv].one_from, bref,
+                                       __builtin_amdgcn_readfirstlane(s_bent[wv]),
+                                       __builtin_amdgcn_readfirstlane(s_bsrc[wv]));
+        m_ex[tid] = (int64_t)ref - (bR + af);
+    } else {
+    if (tried) {  // block maps that did not fit have taken the words' place
+        __syncthreads();
+        m_lo[tid] = valid ? sp[SP_LO * ns] : 0;
+        m_hi[tid] = valid ? sp[SP_HI * ns] : 0;
+        m_af[tid] = valid ? sp[SP_AF * ns] : 0;
+        m_kf[tid] = valid ? sp[SP_KF * ns] : 0;
+    }
+    // sparse tiles: the walker reads footprint offsets inside the tile from
+    // LDS instead of scanning each group of 64 segments it enters
+    if (sparse) m_R[tid] = rF;
+    if (sparse || tried) __syncthreads();
     if (wv == 0) {
         // ---- the walker ----
         int q = 0;  // SIM segments passed, in walk order
@@ -1604,14 +2294,15 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
         // into pf while the current stop is resolved (pf_lane: its tile lane,
         // -1 if none).  At a stop they are written to ring slot 0 (unused in
         // sparse tiles; the write waits only for loads the stop needs) and
-        // the registers take the next prediction's loads at once.
-        int64_t pf[NW];
+        // the registers take the next prediction's loads at once.  (32-bit
+        // prefixes only: a stop in another segment loads its own.)
+        int32_t pf[NW];
         int pf_lane = -1;
         auto walk = [&](int b, int e, int64_t x) -> int64_t {
             for (int g0 = b & ~63; g0 < e && ok; g0 += 64) {
                 const int i = g0 + l;
                 const int64_t lo = m_lo[i], hi = m_hi[i], af = m_af[i], kf = m_kf[i];
-                const uint64_t sim = w_sim[g0 >> 6], tot = w_tot[g0 >> 6];
+                const uint64_t sim = w_sim[g0 >> 6], tot = w_tot[g0 >> 6], fits = w_fit[g0 >> 6];
                 const bool is_tot = (tot >> l) & 1;
                 const int64_t S = sparse ? (int64_t)((uint64_t)m_R[i] - (uint64_t)m_R[g0])
                                          : (int64_t)((uint64_t)wave_incl_sum(af) - (uint64_t)af);
@@ -1695,7 +2386,8 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
                             const int c = g0 + stop;
                             const bool one = (uint64_t)hi_c - (uint64_t)lo_c >= (uint64_t)(T - 1) && hi_c >= lo_c;
                             const bool up = xs < lo_c;
-                            if (pf_lane == c) {
+                            const bool fit = (fits >> stop) & 1;
+                            if (pf_lane == c && fit) {
                                 if (one) {
                                     r = exit_one_sample(pf, T, xs, up);
                                 } else {
@@ -1704,7 +2396,7 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
                                 }
                             } else {
                                 int64_t tmp[NW];
-                                load_kept(D, k * TILE + c, tmp);
+                                load_kept(D, k * TILE + c, fit, tmp);
                                 if (one) {
                                     r = exit_one_sample(tmp, T, xs, up);
                                 } else {
@@ -1713,14 +2405,14 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
                                 }
                             }
                             pf_lane = p;
-                            load_kept(D, k * TILE + (p >= 0 ? p : c), pf);
+                            load_kept32(D, k * TILE + (p >= 0 ? p : c), pf);
                             if (!one) r = walk_prefixes(ring[0], T, xs);
                         } else if ((sim >> stop) & 1) {
                             const int slot = q % RING;
                             if (kept && __hip_atomic_load(&r_ready[slot], __ATOMIC_ACQUIRE,
                                                           __HIP_MEMORY_SCOPE_WORKGROUP) != q) {
                                 // its producer is behind: read the kept prefixes instead of waiting
-                                r = walk_kept(D, k * TILE + g0 + stop, T, xs);
+                                r = walk_kept(D, k * TILE + g0 + stop, (fits >> stop) & 1, T, xs);
                             } else {
                                 LocalSpin sp_;
                                 while (__hip_atomic_load(&r_ready[slot], __ATOMIC_ACQUIRE,
@@ -1788,21 +2480,7 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
             }
         }
     } else {
-        if (wv == 1) {
-            // ---- the tile's prefix sums ----
-            int64_t pF = 0, pP = 0, pC = 0;
-            bool ok = true;
-            if (k > 0) {
-                ok = scan_sums(ts, k, pF, pP, pC, ctl);
-                if (l < 3) st_status(ts.at(W_IF + l, k), pack(l == 0 ? pF + tF : (l == 1 ? pP + tP : pC + tC), 1));
-            }
-            if (l == 0) {
-                s_pre[0] = pF;
-                s_pre[1] = pP;
-                s_pre[2] = pC;
-                if (!ok) g_or32(&D.scal->err, 8u);
-            }
-        }
+        if (wv == 1) tile_sums();
         // ---- producers: pre-scan SIM segments in walk order (dense tiles only) ----
         if (!sparse) for (;;) {
             // every lane takes part (lane 0 adds 1, the others 0): a lane-0-only
@@ -1838,11 +2516,12 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
             if (!ok) break;
             // a segment the walker has already passed is not scanned
             if (lane >= 0 && __hip_atomic_load(&s_cons, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= pidx) {
-                if (kept) copy_prefixes(D, k * TILE + lane, ring[slot]);
+                if (kept) copy_prefixes(D, k * TILE + lane, (w_fit[lane >> 6] >> (lane & 63)) & 1, ring[slot]);
                 else prescan_segment(D, k * TILE + lane, ring[slot]);
             }
             __hip_atomic_store(&r_ready[slot], pidx, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
+    }
     }
     __syncthreads();
     const int64_t ef = tid == 0 ? s_entry : m_ex[tid - 1];
@@ -1855,7 +2534,9 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     bool left = false;  // left to the chain pass
     if (valid) {
         const int64_t af = sp[SP_AF * ns], ac = sp[SP_AC * ns];
+        // (read again: kept in registers across the block maps they would spill)
         const int64_t mxf = sp[SP_MXF * ns], mnf = sp[SP_MNF * ns], mxp = sp[SP_MXP * ns], mnp = sp[SP_MNP * ns];
+        const int64_t lo = sp[SP_LO * ns], hi = sp[SP_HI * ns];
         SMP_GLOBAL int64_t* o = gp(D.seg) + j;
         o[SP_F0 * ns] = F0;
         o[SP_P0 * ns] = P0;
@@ -2372,10 +3053,10 @@ __device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, cons
     // Copy volume (section 3.5: one Tc sample per multiple of Tc crossed by
     // the cumulative copy bytes) and the timer split (section 2.1: Python
     // time += quantum, native time += delay) go to the lines' counters here.
-    // Only a segment that holds such events (summary flag bit 2) looks for
+    // Only a segment that holds such events (FLG_AUX) looks for
     // them, and only one whose copy bytes cross a multiple of Tc holds a copy
     // sample and scans its copy bytes.
-    const bool has_aux = (readlane64(pv, 19) & 4) != 0;
+    const bool has_aux = (readlane64(pv, 19) & FLG_AUX) != 0;
     int64_t cc = 0;
     bool csmp = false;
     if (has_aux) {

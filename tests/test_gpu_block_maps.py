@@ -1,0 +1,69 @@
+"""Block maps of the resolve pass (64 segments of 512 events followed for all
+entries at once) against the oracle: every output exact, as everywhere.
+
+The sizes are the edges of segments, blocks and tiles; the thresholds go from
+many samples in a segment to entries that stay unsampled past the block's
+limit (the tile is walked instead), and past the 32-bit range of the maps."""
+import numpy as np
+import pytest
+
+import oracle
+import tracegen as tg
+from parity_util import compare
+
+pytestmark = pytest.mark.gpu
+
+SEG, BLK, TILE = 512, 64 * 512, 512 * 512
+
+
+@pytest.fixture(scope="module")
+def sampler():
+    import paper_2212_07597_amd as smp
+    s = smp.Sampler(workspace=4 << 30)
+    yield s
+    s.close()
+
+
+def check(sampler, cases):
+    import paper_2212_07597_amd as smp
+    print("block maps:", [c[0] for c in cases], flush=True)
+    ids = [sampler.submit_trace(ev, smp.make_params(kw["threshold"], kw["num_lines"], kw.get("copy_threshold")))
+           for _, ev, kw in cases]
+    sampler.run(blocking=True)
+    for t, (label, ev, kw) in zip(ids, cases):
+        compare(sampler.fetch_profile(t), oracle.run(ev, **kw), label)
+
+
+@pytest.mark.parametrize("T", [tg.MiB // 2 + 1, 2 * tg.MiB, 3 * tg.MiB + 1, 10 * tg.MiB, 24 * tg.MiB, 40 * tg.MiB])
+def test_sizes(sampler, T):
+    """Block and tile edges, alone and in one launch."""
+    ev = tg.mix(77, 2 * TILE + BLK + 300, num_lines=50, copy_frac=0.05, timer_frac=0.01)
+    sizes = [7 * SEG, 8 * SEG, 9 * SEG + 1, BLK - 1, BLK, BLK + 1, BLK + SEG + 3, 5 * BLK + 31, TILE, TILE + 20,
+             2 * TILE + BLK + 300]
+    cases = [(f"n{n} T{T}", ev[:n], dict(threshold=T, num_lines=50)) for n in sizes]
+    check(sampler, cases)
+    for c in cases[-3:]:
+        check(sampler, [c])
+
+
+def test_mixed_segments(sampler):
+    """Segments every entry samples in, segments with one exit and segments
+    that depend on the entry, side by side; a footprint that drifts; sizes up
+    to and past the 32-bit range of the maps."""
+    rng = np.random.default_rng(5)
+    n = 3 * BLK + 1000
+    base = tg.mix(78, n, num_lines=9)
+    forced = base.copy()
+    at = rng.choice(n, 40, replace=False)
+    forced["delta"][at] = np.where(rng.random(40) < 0.5, 1, -1) * 25 * tg.MiB
+    forced["flags"][at] = 1
+    quiet = base.copy()  # stretches of small steps between loud ones
+    quiet["delta"][(np.arange(n) // 3000) % 2 == 1] //= 64
+    wide = tg.mix(79, n, num_lines=9, size_lo=1 << 20, size_hi=1 << 27)
+    edge = tg.mix(80, n, num_lines=9, size_lo=1 << 10, size_hi=1 << 20)
+    edge["delta"][::7000] = (1 << 30) - 7
+    edge["delta"][3::7000] = -(1 << 30) + 7
+    cases = [("forced", forced, 10 * tg.MiB), ("forced small T", forced, 3 * tg.MiB), ("quiet", quiet, 10 * tg.MiB),
+             ("quiet small T", quiet, 2 * tg.MiB), ("wide", wide, (1 << 29) + 1), ("wide below", wide, (1 << 30) - 1),
+             ("wide at", wide, 1 << 30), ("edge", edge, 10 * tg.MiB), ("edge high", edge, (1 << 30) - 1)]
+    check(sampler, [(label, ev, dict(threshold=T, num_lines=9)) for label, ev, T in cases])
