@@ -6,11 +6,11 @@
 // cumulative bytes allocated plus bytes freed by memory events; the samples
 // are attributed to the event's line.
 //
-// Three kernels over the records (one wave per 512-event segment, as in the
-// threshold sampler): the volume of each segment; one workgroup's exclusive
-// scan of the segment volumes (with the status and the total count); and the
-// per-event counts, whose first multiple of T comes from the previous lane's
-// quotient, added per line through an LDS cache.
+// One kernel over the records: a workgroup holds a tile of them in registers,
+// publishes the tile's volume, takes the volume before it from a look-back
+// over the tiles before and counts each event's samples from the registers,
+// per line through an LDS cache.  A small kernel before it clears the counts
+// and the look-back's words.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -25,10 +25,13 @@ constexpr int RATE_SLOTS = 256;            // LDS line cache of the count kernel
 constexpr uint32_t NO_LINE = 0xFFFFFFFFu;
 constexpr uint64_t VOL_LIMIT = 1ull << 62;  // volumes at or above it: SMP_EOVERFLOW
 
-// Workspace: a header (word 0: flags, bit 0 = a malformed record; words
-// 1-16: the scan's span offsets), then one volume per segment (after the
-// scan: the volume before the segment, relative to its span).
+// Workspace: a header of 64-bit words, then one look-back word per tile
+// (2-bit state: 1 the tile's own volume, 2 the volume through it; 62-bit
+// volume).
 constexpr uint64_t RATE_HDR = 256;
+constexpr uint64_t RATE_BIG = 512ull << 10;  // events above which tiles are large
+enum { RH_FLAGS = 0, RH_DONE, RH_TOTAL, RH_TICKET, RH_WORDS };  // flags, workgroups finished, volume, next tile
+enum { RF_BAD = 1, RF_OVERFLOW = 2, RF_FAULT = 4 };
 
 struct RateRec {
     int64_t delta;
@@ -67,97 +70,43 @@ __device__ __forceinline__ uint64_t rate_volume(const RateRec& r, bool valid, ui
     return mem ? (r.delta < 0 ? (uint64_t)(-r.delta) : d) : 0;
 }
 
-__device__ __forceinline__ int rate_seg_events(uint64_t n, uint64_t j) {
-    const uint64_t a = j * SEG;
-    return (int)((n - a) < (uint64_t)SEG ? (n - a) : (uint64_t)SEG);
-}
-
-__global__ void k_rate_clear(int64_t* counts, uint32_t L, uint64_t* result, uint64_t* flags) {
+__global__ void k_rate_clear(int64_t* counts, uint32_t L, uint64_t* result, uint64_t* hdr, uint64_t ntile) {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < L) gp(counts)[i] = 0;
     if (i < 2) gp(result)[i] = 0;
-    if (i == 0) *gp(flags) = 0;
+    if (i < RH_WORDS) gp(hdr)[i] = 0;
+    if (i < ntile) gp(hdr)[RATE_HDR / 8 + i] = 0;
 }
 
-// Volume of each segment (one wave per segment).
-__global__ __launch_bounds__(BLOCK) void k_rate_sums(const uint8_t* __restrict__ ev, uint64_t n, uint64_t nseg,
-                                                     uint32_t L, uint64_t* vol, uint64_t* flags) {
-    const uint64_t j = (uint64_t)blockIdx.x * WAVES + (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (j >= nseg) return;
-    const int nv = rate_seg_events(n, j);
-    ru8_t* base = (ru8_t*)(ev + j * SEG * 24);
-    RateRec r[NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) r[w] = rate_load(base, nv, w);
+constexpr uint64_t VOL_MASK = (1ull << 62) - 1;
+constexpr uint32_t RATE_SPINS = 1u << 24;
+
+// Volume before tile t (one wave): 64 tiles per probe, nearest first, up to
+// the nearest one that knows the volume through it.  (Volumes whose sum
+// reaches 2^62 are flagged by the first tile that sees them: every sum up to
+// there is exact.)  Probes of 256 or 512 tiles measured 3 to 10 % slower.
+__device__ bool rate_lookback(const uint64_t* st, int64_t t, uint64_t& excl) {
+    const int l = lane_id();
     uint64_t acc = 0;
-    uint64_t badm = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        bool bad;
-        acc += rate_volume(r[w], w * 64 + lane_id() < nv, L, bad);  // < 8 x 2^52 per lane
-        badm |= ballot(bad);
-    }
-    const uint64_t s = (uint64_t)wave_sum((int64_t)acc);  // < 2^61
-    if (lane_id() == 0) {
-        gp(vol)[j] = s;
-        if (badm) __hip_atomic_fetch_or(gp(flags), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
-// Exclusive scan of the segment volumes in place, by one workgroup of 16
-// waves: wave w scans span w (P consecutive segments) 64 at a time with
-// coalesced loads, eight groups in flight, and writes prefixes relative to
-// the span start; the span offsets go to hdr[1..16].  The exact total is kept
-// as separate sums of the volumes' high and low 32-bit halves, which cannot
-// wrap (a segment's volume is below 2^61); every prefix is exact when the
-// total is below 2^62, and a larger total is reported as SMP_EOVERFLOW
-// (a malformed record wins over it).
-__global__ __launch_bounds__(1024) void k_rate_scan(uint64_t* vol, uint64_t nseg, uint64_t P, int64_t T,
-                                                    uint64_t* result, uint64_t* hdr) {
-    __shared__ uint64_t w_tot[16], w_hi[16], w_lo[16];
-    const int wv = threadIdx.x >> 6, l = lane_id();
-    const uint64_t b = (uint64_t)wv * P;
-    const uint64_t e = b + P < nseg ? b + P : nseg;
-    SMP_GLOBAL uint64_t* v = gp(vol);
-    uint64_t carry = 0, shi = 0, slo = 0;
-    for (uint64_t g = b; g < e; g += 8 * 64) {
-        uint64_t x[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const uint64_t i = g + (uint64_t)(k * 64 + l);
-            x[k] = i < e ? v[i] : 0;
+    int64_t base = t - 1;
+    for (uint32_t spins = 0; spins < RATE_SPINS;) {
+        const int64_t j = base - l;
+        const uint64_t w = j >= 0 ? ld_status(st + j) : 2ull << 62;  // before the first tile: nothing
+        const uint64_t inc = ballot((w >> 62) == 2);
+        const int lim = inc ? ctz64(inc) : 63;
+        if (ballot(l <= lim && (w >> 62) == 0)) {  // one of them is not there yet
+            ++spins;
+            __builtin_amdgcn_s_sleep(4);
+            continue;
         }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            shi += x[k] >> 32;
-            slo += x[k] & 0xFFFFFFFFull;
-            const uint64_t inc = (uint64_t)wave_incl_sum((int64_t)x[k]);
-            const uint64_t i = g + (uint64_t)(k * 64 + l);
-            if (i < e) v[i] = carry + inc - x[k];
-            carry += readlaneu64(inc, 63);
+        acc += (uint64_t)wave_sum((int64_t)(l <= lim ? w & VOL_MASK : 0));
+        if (inc) {
+            excl = acc;
+            return true;
         }
+        base -= 64;
     }
-    shi = (uint64_t)wave_sum((int64_t)shi);
-    slo = (uint64_t)wave_sum((int64_t)slo);
-    if (l == 0) {
-        w_tot[wv] = carry;
-        w_hi[wv] = shi;
-        w_lo[wv] = slo;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t off = 0, H = 0, Lo = 0;
-        for (int w = 0; w < 16; ++w) {
-            gp(hdr)[1 + w] = off;
-            off += w_tot[w];
-            H += w_hi[w];  // < 2^53 in all
-            Lo += w_lo[w]; // < 2^56 in all
-        }
-        const bool ovf = H >= (1ull << 30) || (H << 32) + Lo >= VOL_LIMIT;
-        const uint64_t f = *gp(hdr);
-        gp(result)[1] = (f & 1) ? (uint64_t)SMP_EINVAL : (ovf ? (uint64_t)SMP_EOVERFLOW : (uint64_t)SMP_OK);
-        gp(result)[0] = ovf ? 0 : ((H << 32) + Lo) / (uint64_t)T;
-    }
+    return false;
 }
 
 struct RateCache {
@@ -175,54 +124,159 @@ __device__ __forceinline__ void rate_add(RateCache& c, int64_t* counts, uint32_t
         g_add((uint64_t*)&counts[line], v);
 }
 
-// Per-event counts and their per-line sums (grid-stride over segments, one
-// wave per segment).  Lane l's count is floor(b_l / T) - floor(b_(l-1) / T),
-// b_l the volume through its record; the second quotient is the previous
-// lane's first (the previous window's last lane for lane 0).
-__global__ __launch_bounds__(BLOCK) void k_rate_count(const uint8_t* __restrict__ ev, uint64_t n, uint64_t nseg,
-                                                      uint64_t P, uint32_t L, int64_t T, const uint64_t* vol,
-                                                      const uint64_t* hdr, int64_t* counts, const uint64_t* result) {
+// floor(u / T) for u < 2^62 with m = floor((2^64 - 1) / T): the high product
+// is the quotient or one less.  rem receives u mod T.
+__device__ __forceinline__ uint64_t rate_div(uint64_t u, uint64_t T, uint64_t m, uint64_t& rem) {
+    uint64_t q = __umul64hi(u, m);
+    uint64_t r = u - q * T;
+    const bool up = r >= T;
+    q += up ? 1 : 0;
+    r -= up ? T : 0;
+    rem = r;
+    return q;
+}
+
+// Persistent workgroups take tiles by ticket, so every tile that a look-back
+// waits on belongs to a running workgroup, which depends on earlier tiles
+// only.  Lane
+// l's count is floor(b_l / T) - floor(b_(l-1) / T), b_l the volume through
+// its record, taken modulo T at each window's start; a window whose volume
+// does not reach the next multiple of T is passed over, and the divisions of
+// the others are products with a reciprocal.
+// Bound: HBM reads (24 bytes per event, once) and the look-back's latency (the
+// same kernel without its waits: 0.48 ms).  One call on 1e8 events at T = 10
+// MiB: 0.57 ms, 4.2 TB/s; as two passes over the records with a scan between
+// them it took 0.92 ms.  1e5 events: 17.5 -> 13 us (two launches, not four).
+template <int WV>
+__global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(4))) void k_rate(const uint8_t* __restrict__ ev, uint64_t n, uint64_t ntile,
+                                                     uint32_t L, int64_t T, uint64_t m, uint64_t* hdr,
+                                                     int64_t* counts, uint64_t* result) {
+    constexpr int BLK = 64 * WV, TILE_EV = SEG * WV;  // one segment per wave
     __shared__ RateCache c;
-    for (int i = threadIdx.x; i < RATE_SLOTS; i += blockDim.x) {
+    __shared__ uint64_t s_sum[WV];
+    __shared__ uint64_t s_excl, s_tk, s_last;
+    const int tid = threadIdx.x, l = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = tid; i < RATE_SLOTS; i += BLK) {
         c.key[i] = NO_LINE;
         c.cnt[i] = 0;
     }
-    __syncthreads();
-    // nothing to count for a malformed or overflowing trace
-    const bool ok = *gp(result + 1) == (uint64_t)SMP_OK;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t stride = (uint64_t)gridDim.x * WAVES;
+    uint64_t* st = hdr + RATE_HDR / 8;
     const uint64_t uT = (uint64_t)T;
-    for (uint64_t j = (uint64_t)blockIdx.x * WAVES + wv; ok && j < nseg; j += stride) {
-        const int nv = rate_seg_events(n, j);
-        ru8_t* base = (ru8_t*)(ev + j * SEG * 24);
-        RateRec r[NW];
+    // The tile in hand: its records' volumes and lines, the sum of the waves'
+    // volumes before this wave.  The next one: its records, loading.
+    uint64_t vol[NW], before = 0, agg = 0;
+    uint32_t line[NW];
+    RateRec r[NW];
+    auto valid_of = [&](uint64_t t) {
+        const uint64_t a = t * TILE_EV + (uint64_t)wv * SEG;
+        return t >= ntile || a >= n ? 0 : (int)(n - a < (uint64_t)SEG ? n - a : (uint64_t)SEG);
+    };
+    auto take_ticket = [&]() -> uint64_t {
+        __syncthreads();
+        if (tid == 0) s_tk = g_add_rtn(hdr + RH_TICKET, 1ull);
+        __syncthreads();
+        return readlaneu64(s_tk, 0);
+    };
+    auto load_tile = [&](uint64_t t) {
+        const int nv = valid_of(t);
+        // (a wave past the end re-reads the last record, whose volume is masked)
+        const uint64_t a = t * TILE_EV + (uint64_t)wv * SEG;
+        ru8_t* base = (ru8_t*)(ev + (nv ? a : n - 1) * 24);
 #pragma unroll
-        for (int w = 0; w < NW; ++w) r[w] = rate_load(base, nv, w);
-        // the volume before the segment (wave-uniform)
-        uint64_t run = readlaneu64(gp(vol)[j] + gp(hdr)[1 + j / P], 0);
-        uint64_t q = run / uT;
+        for (int w = 0; w < NW; ++w) r[w] = rate_load(base, nv ? nv : 1, w);
+    };
+    // the loaded tile becomes the one in hand, its volume published
+    auto take_tile = [&](uint64_t t) {
+        const int nv = valid_of(t);
+        uint64_t acc = 0, badm = 0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             bool bad;
-            const uint64_t a = rate_volume(r[w], w * 64 + lane_id() < nv, L, bad);
-            const uint64_t bv = (uint64_t)wave_incl_sum((int64_t)a) + run;
-            const uint64_t qb = bv / uT;
-            const uint64_t qa = (uint64_t)wave_shr1((int64_t)qb, (int64_t)q);
-            const uint64_t cnt = qb - qa;
-            if (cnt) rate_add(c, counts, r[w].line, cnt);
-            run = readlaneu64(bv, 63);
-            q = readlaneu64(qb, 63);
+            vol[w] = rate_volume(r[w], w * 64 + l < nv, L, bad);
+            line[w] = r[w].line;
+            acc += vol[w];  // < 8 x 2^52 per lane
+            badm |= ballot(bad);
         }
+        const uint64_t mine = (uint64_t)wave_sum((int64_t)acc);  // < 2^61
+        if (l == 0) s_sum[wv] = mine;
+        if (badm && l == 0) g_or(hdr + RH_FLAGS, RF_BAD);
+        __syncthreads();
+        before = agg = 0;  // < 2^64
+        for (int w = 0; w < WV; ++w) {
+            if (w == wv) before = agg;
+            agg += s_sum[w];
+        }
+        if (tid == 0) st_status(st + t, (agg & VOL_MASK) | (t == 0 ? 2ull : 1ull) << 62);
+    };
+    uint64_t t = take_ticket();
+    if (t < ntile) {
+        load_tile(t);
+        take_tile(t);
+    }
+    while (t < ntile) {
+        // (no more tiles than workgroups: each has its one)
+        const uint64_t tn = ntile > gridDim.x ? take_ticket() : ntile;
+        if (tn < ntile) load_tile(tn);
+        if (wv == 0) {
+            uint64_t excl = 0;
+            const bool ok = t == 0 || rate_lookback(st, (int64_t)t, excl);
+            const uint64_t incl = excl + agg;
+            if (l == 0) {
+                st_status(st + t, (incl & VOL_MASK) | 2ull << 62);
+                s_excl = excl;
+                const uint32_t f = (agg >= VOL_LIMIT || excl >= VOL_LIMIT || incl >= VOL_LIMIT ? RF_OVERFLOW : 0) |
+                                   (ok ? 0 : RF_FAULT);
+                if (f) g_or(hdr + RH_FLAGS, f);
+                if (t == ntile - 1) st_status(hdr + RH_TOTAL, incl);
+            }
+        }
+        __syncthreads();
+        uint64_t rem;
+        (void)rate_div(readlaneu64(s_excl + before, 0) & VOL_MASK, uT, m, rem);
+        rem = readlaneu64(rem, 0);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const uint64_t u = (uint64_t)wave_incl_sum((int64_t)vol[w]) + rem;
+            const uint64_t last = readlaneu64(u, 63);
+            if (last >= uT) {
+                uint64_t q_rem;
+                const uint64_t q = rate_div(u, uT, m, q_rem);
+                const uint64_t cnt = q - (uint64_t)wave_shr1((int64_t)q, 0);
+                if (cnt) rate_add(c, counts, line[w], cnt);
+                rem = readlaneu64(q_rem, 63);
+            } else {
+                rem = last;
+            }
+        }
+        if (tn < ntile) take_tile(tn);
+        t = tn;
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < RATE_SLOTS; i += blockDim.x) {
+    for (int i = tid; i < RATE_SLOTS; i += BLK) {
         const uint32_t k = c.key[i];
         if (k != NO_LINE && c.cnt[i]) g_add((uint64_t*)&counts[k], c.cnt[i]);
     }
+    // The last workgroup to finish writes the status and the total.  (What the
+    // others wrote went to memory by agent-scope atomics: complete once this
+    // fence has waited for them, with no cache to write back.)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __syncthreads();
+    if (tid == 0) s_last = g_add_rtn(hdr + RH_DONE, 1ull);
+    __syncthreads();
+    if (s_last != (uint64_t)gridDim.x - 1) return;
+    const uint64_t f = ld_status(hdr + RH_FLAGS), total = ld_status(hdr + RH_TOTAL);
+    if (f) {  // nothing to count for a malformed or overflowing trace
+        for (uint64_t i = tid; i < L; i += BLK) gp(counts)[i] = 0;
+    }
+    if (tid == 0) {
+        const bool ovf = (f & RF_OVERFLOW) != 0;
+        gp(result)[1] = (f & RF_BAD) ? (uint64_t)SMP_EINVAL
+                                     : ((f & RF_FAULT) ? (uint64_t)SMP_EDEVICE
+                                                       : (ovf ? (uint64_t)SMP_EOVERFLOW : (uint64_t)SMP_OK));
+        gp(result)[0] = ovf ? 0 : total / uT;
+    }
 }
-
-int g_count_grid = 0;
 
 bool rate_args_ok(const smp_event_t* ev, uint64_t n, int64_t threshold, uint32_t num_lines, int64_t* line_counts,
                   uint64_t* result) {
@@ -234,33 +288,35 @@ bool rate_args_ok(const smp_event_t* ev, uint64_t n, int64_t threshold, uint32_t
 // header, then 8 bytes per segment).
 int rate_launch(const smp_event_t* ev, uint64_t n, int64_t threshold, uint32_t num_lines, void* ws,
                 int64_t* line_counts, uint64_t* result, hipStream_t s) {
-    uint64_t* flags = (uint64_t*)ws;
-    uint64_t* vol = (uint64_t*)((uint8_t*)ws + RATE_HDR);
-    const uint64_t nseg = (n + SEG - 1) / SEG;
-    const uint32_t cl = num_lines > 2 ? num_lines : 2;
-    // a kernel, not a memset, clears the counts, the result and the flags
-    k_rate_clear<<<dim3((cl + 255) / 256), dim3(256), 0, s>>>(line_counts, num_lines, result, flags);
+    // Tiles of 8 segments up to RATE_BIG events, of 16 above: the large ones
+    // halve the look-back's steps and the line caches that are flushed, the
+    // small ones give short traces more workgroups.  Small against large: 1e5
+    // events 13.0 / 14.8 us, 4e5 18.1 / 17.7, 1e6 31.5 / 24.0 (64 lines) and
+    // 15.2 / 16.8 (10,000 lines), 3e6 66 / 41 and 35 / 31, 1e8 741 / 597.
+    const bool big = n > RATE_BIG;
+    const uint64_t te = (uint64_t)SEG * (big ? 16 : 8);
+    const uint64_t ntile = (n + te - 1) / te;
+    uint64_t* hdr = (uint64_t*)ws;
+    uint64_t cl = num_lines > RH_WORDS ? num_lines : RH_WORDS;
+    if (cl < ntile) cl = ntile;
+    // a kernel, not a memset, clears the counts, the result and the words of the look-back
+    k_rate_clear<<<dim3((unsigned)((cl + 255) / 256)), dim3(256), 0, s>>>(line_counts, num_lines, result, hdr, ntile);
     if (hipGetLastError() != hipSuccess) return SMP_EDEVICE;
-    if (nseg == 0) {
+    if (ntile == 0) {
         // no events: K = 0, status OK (the clear wrote both)
         return SMP_OK;
     }
-    const uint8_t* e = (const uint8_t*)ev;
-    k_rate_sums<<<dim3((unsigned)((nseg + WAVES - 1) / WAVES)), dim3(BLOCK), 0, s>>>(e, n, nseg, num_lines, vol, flags);
-    const uint64_t P = (nseg + 15) / 16;  // segments per span of the scan
-    k_rate_scan<<<dim3(1), dim3(1024), 0, s>>>(vol, nseg, P, threshold, result, flags);
-    if (g_count_grid <= 0) {
-        int dev = 0, cus = 0, per = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void*)k_rate_count, BLOCK, 0) != hipSuccess)
-            return SMP_EDEVICE;
-        g_count_grid = cus * (per > 0 ? per : 1);
-    }
-    const uint64_t wgs = (nseg + WAVES - 1) / WAVES;
-    const unsigned grid = (unsigned)(wgs < (uint64_t)g_count_grid ? wgs : (uint64_t)g_count_grid);
-    k_rate_count<<<dim3(grid), dim3(BLOCK), 0, s>>>(e, n, nseg, P, num_lines, threshold, vol, flags, line_counts,
-                                                    result);
+    // as many workgroups as a device of 256 CUs holds at once (two of 16 waves
+    // do not fit one CU); more tiles are taken by the same workgroups
+    const uint64_t lim = big ? 256 : 512;
+    const unsigned grid = (unsigned)(ntile < lim ? ntile : lim);
+    const uint64_t m = ~0ull / (uint64_t)threshold;
+    if (big)
+        k_rate<16><<<dim3(grid), dim3(1024), 0, s>>>((const uint8_t*)ev, n, ntile, num_lines, threshold, m, hdr,
+                                                     line_counts, result);
+    else
+        k_rate<8><<<dim3(grid), dim3(512), 0, s>>>((const uint8_t*)ev, n, ntile, num_lines, threshold, m, hdr,
+                                                   line_counts, result);
     return hipGetLastError() == hipSuccess ? SMP_OK : SMP_EDEVICE;
 }
 
