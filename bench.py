@@ -16,10 +16,9 @@ kernel (the slowest of the five sampling passes; its algorithmic bytes are
 the 24-byte record of every event, over that kernel's own HIP-event duration
 in the serialized steps), the whole launch against the same bytes, and the
 CPU oracle timed on one pinned host core as a baseline.  The per-pass
-breakdown (pass_ms, kernel_ms) comes from untimed steps that record events
-around every pass; the serialized steps record only the two around the
-dominant pass, because each event between two kernels idles the GPU for a
-few microseconds.  An end-to-end figure (pinned host events -> HBM, the
+breakdown (pass_ms, kernel_ms) comes from untimed steps that record the
+start of every pass; the serialized steps record only the two times around
+the dominant pass.  An end-to-end figure (pinned host events -> HBM, the
 launch, and the full profile copied back) is reported beside it, never as
 `value`.
 
@@ -232,7 +231,7 @@ def main():
 
     # Per-pass breakdown (untimed): events around every pass.  It names the
     # dominant pass; the timed loop then records only the two events around
-    # that pass, since each event between kernels idles the GPU.
+    # that pass.
     pass_ms, main_list, launch_list = [], [], []
     for _ in range(max(args.warmup, 3)):
         tid = step()

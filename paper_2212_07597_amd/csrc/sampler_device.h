@@ -140,6 +140,13 @@ struct Desc {
     uint32_t pad_;
 };
 
+// Ranges of a trace's results to copy out (8-byte words; at: place in the destination).
+struct CopyOut {
+    const uint64_t* src[3];
+    uint64_t words[3];
+    uint64_t at[3];
+};
+
 // ---- wave64 helpers -------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 

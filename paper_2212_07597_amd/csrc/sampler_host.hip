@@ -18,10 +18,12 @@ int emit_grid_limit();
 int track_grid_limit();
 hipError_t launch_clear(const Desc* desc, int ntraces, uint64_t total_bytes, unsigned long long* ctl, hipStream_t s);
 hipError_t launch_pass(int pass, const Desc* desc, int ntraces, uint64_t nseg_total, uint64_t ntile_total,
-                       unsigned long long* ctl, int grid_limit, hipStream_t s);
+                       unsigned long long* ctl, int grid_limit, uint64_t* ts, hipStream_t s);
 hipError_t launch_finish(const Desc* desc, int ntraces, uint64_t nblk_total, uint64_t total_lines,
-                         unsigned long long* ctl, int track_grid, Scalars* gather, hipStream_t s);
-hipError_t launch_tmap(const Desc* desc, int ntraces, uint64_t ntile_total, unsigned long long* ctl, hipStream_t s);
+                         unsigned long long* ctl, int track_grid, Scalars* gather, uint64_t* ts, hipStream_t s);
+hipError_t launch_tmap(const Desc* desc, int ntraces, uint64_t ntile_total, unsigned long long* ctl, uint64_t* ts,
+                       hipStream_t s);
+hipError_t launch_copy_out(const CopyOut& c, uint64_t* dst, hipStream_t s);
 }  // namespace smp
 
 using namespace smp;
@@ -44,6 +46,11 @@ constexpr int LAUNCH_STREAMS = 2;
 constexpr int MAX_TRACES_PER_RUN = 4096;
 constexpr uint64_t CBLK_WORDS = 256;
 constexpr int NPASS = 5;  // summarize, resolve, chain, scan, emit
+// Profiles up to this size are copied out through the sampler's own pinned
+// buffer by one kernel and one wait (a profile of 130 to 260 KB: about 30 us
+// instead of 75 to 100 for five blocking copies), larger ones by copies
+// straight into the caller's arrays, all queued before one wait.
+constexpr uint64_t FETCH_STAGE = 1ull << 20;
 constexpr uint32_t TILE_MAP_TILES_DEFAULT = 64;  // traces of at least this many tiles get tile maps
 
 uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
@@ -187,8 +194,11 @@ struct RunSlot {
     hipStream_t stream = nullptr;  // the slot's current launch (one of the sampler's launch streams)
     hipEvent_t e_ready = nullptr;  // recorded on the caller's stream at run()
     hipEvent_t e_start = nullptr, e_end = nullptr;
-    hipEvent_t e_pass[NPASS + 1] = {};  // around each pass of the sampling kernels
-    uint32_t ev_mask = 0;               // which e_pass events this launch recorded
+    // The device clock at the start of each pass and after the last one
+    // (written by the kernels into pinned, coherent host memory)
+    uint64_t* host_ts = nullptr;
+    uint64_t* host_ts_dev = nullptr;
+    uint32_t ev_mask = 0;               // which of them this launch records
     bool busy = false;
     uint64_t seq = 0;
     LaunchKey last_key{};               // shape of the slot's previous launch
@@ -216,6 +226,15 @@ struct smp_sampler {
     uint64_t next_id = 1;
     uint64_t run_seq = 0;
     int grid_chain = 0, grid_emit = 0, grid_track = 0;
+    double clock_khz = 0;           // rate of the device clock
+    hipStream_t fetch_stream = nullptr;
+    // Pinned host memory, one block for all slots each: their descriptor
+    // staging; and, coherent, their scalars and start times and the copy-out
+    // buffer (an allocation each would take most of sampler_create's time)
+    Desc* pin_desc = nullptr;
+    uint8_t* pin = nullptr;
+    uint8_t* stage = nullptr;       // FETCH_STAGE bytes of it
+    uint64_t* stage_dev = nullptr;  // their device address
     bool failed = false;
     float last_main_ms = 0, last_total_ms = 0;
     float last_pass_ms[NPASS] = {};
@@ -289,11 +308,14 @@ int retire_slot(smp_sampler* s, RunSlot& r) {
     // intervals whose two events were not recorded read -1
     float a = -1, b = -1, p[NPASS];
     const uint32_t m = r.ev_mask;
-    if ((m & 1u) && ((m >> NPASS) & 1u)) HIPCHK(hipEventElapsedTime(&a, r.e_pass[0], r.e_pass[NPASS]));
+    auto between = [&](int i, int j) {  // (a launch of empty traces holds no pass)
+        return r.last_key.seg ? (float)((double)(int64_t)(r.host_ts[j] - r.host_ts[i]) / s->clock_khz) : 0.0f;
+    };
+    if ((m & 1u) && ((m >> NPASS) & 1u)) a = between(0, NPASS);
     if ((m >> START_EVENT_BIT) & 1u) HIPCHK(hipEventElapsedTime(&b, r.e_start, r.e_end));
     for (int i = 0; i < NPASS; ++i) {
         p[i] = -1;
-        if (((m >> i) & 1u) && ((m >> (i + 1)) & 1u)) HIPCHK(hipEventElapsedTime(&p[i], r.e_pass[i], r.e_pass[i + 1]));
+        if (((m >> i) & 1u) && ((m >> (i + 1)) & 1u)) p[i] = between(i, i + 1);
     }
     if (r.seq >= s->last_seq) {
         s->last_seq = r.seq;
@@ -366,26 +388,39 @@ int sampler_create(int device, void* hip_stream, uint64_t mem_budget, void* work
             return SMP_EDEVICE;
         }
     }
+    int khz = 0;
+    constexpr uint64_t scal_bytes = sizeof(Scalars) * MAX_TRACES_PER_RUN, ts_bytes = 64;
+    static_assert(ts_bytes >= 8 * (NPASS + 1), "start times of a launch");
+    uint8_t* pin_dev = nullptr;
+    if (hipStreamCreateWithFlags(&s->fetch_stream, hipStreamNonBlocking) != hipSuccess ||
+        hipHostMalloc((void**)&s->pin_desc, sizeof(Desc) * MAX_TRACES_PER_RUN * RUN_SLOTS, hipHostMallocDefault) !=
+            hipSuccess ||
+        hipHostMalloc((void**)&s->pin, FETCH_STAGE + (scal_bytes + ts_bytes) * RUN_SLOTS, hipHostMallocCoherent) !=
+            hipSuccess ||
+        hipHostGetDevicePointer((void**)&pin_dev, s->pin, 0) != hipSuccess ||
+        hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz <= 0) {
+        sampler_destroy(s);
+        return SMP_EDEVICE;
+    }
+    s->clock_khz = khz;
+    s->stage = s->pin;
+    s->stage_dev = (uint64_t*)pin_dev;
     for (int i = 0; i < RUN_SLOTS; ++i) {
         RunSlot& r = s->slots[i];
         uint8_t* base = s->ws + i * slot_bytes();
         r.dev_desc = (Desc*)base;
         r.dev_ticket = (unsigned long long*)(base + align_up(sizeof(Desc) * MAX_TRACES_PER_RUN, ALIGN));
-        if (hipHostMalloc((void**)&r.host_desc, sizeof(Desc) * MAX_TRACES_PER_RUN, hipHostMallocDefault) != hipSuccess ||
-            hipHostMalloc((void**)&r.host_scal, sizeof(Scalars) * MAX_TRACES_PER_RUN, hipHostMallocCoherent) !=
-                hipSuccess ||
-            hipHostGetDevicePointer((void**)&r.host_scal_dev, r.host_scal, 0) != hipSuccess ||
-            hipEventCreateWithFlags(&r.e_ready, hipEventDisableTiming) != hipSuccess ||
+        r.host_desc = s->pin_desc + (uint64_t)i * MAX_TRACES_PER_RUN;
+        const uint64_t at = FETCH_STAGE + i * (scal_bytes + ts_bytes);
+        r.host_scal = (Scalars*)(s->pin + at);
+        r.host_scal_dev = (Scalars*)(pin_dev + at);
+        r.host_ts = (uint64_t*)(s->pin + at + scal_bytes);
+        r.host_ts_dev = (uint64_t*)(pin_dev + at + scal_bytes);
+        if (hipEventCreateWithFlags(&r.e_ready, hipEventDisableTiming) != hipSuccess ||
             hipEventCreate(&r.e_start) != hipSuccess || hipEventCreate(&r.e_end) != hipSuccess ||
             !(r.last_desc = new (std::nothrow) Desc[MAX_TRACES_PER_RUN])) {
             sampler_destroy(s);
             return SMP_EDEVICE;
-        }
-        for (auto& e : r.e_pass) {
-            if (hipEventCreate(&e) != hipSuccess) {
-                sampler_destroy(s);
-                return SMP_EDEVICE;
-            }
         }
     }
     s->grid_chain = chain_grid_limit();
@@ -406,19 +441,18 @@ void sampler_destroy(smp_sampler_t* s) {
             if (r.busy && r.e_end) (void)hipEventSynchronize(r.e_end);
     }
     for (auto& r : s->slots) {
-        if (r.host_desc) (void)hipHostFree(r.host_desc);
         delete[] r.last_desc;
         r.last_desc = nullptr;
-        if (r.host_scal) (void)hipHostFree(r.host_scal);
         if (r.e_ready) (void)hipEventDestroy(r.e_ready);
         if (r.e_start) (void)hipEventDestroy(r.e_start);
-        for (auto& e : r.e_pass)
-            if (e) (void)hipEventDestroy(e);
         if (r.e_end) (void)hipEventDestroy(r.e_end);
         if (r.gexec) (void)hipGraphExecDestroy(r.gexec);
     }
     for (auto& st : s->streams)
         if (st) (void)hipStreamDestroy(st);
+    if (s->fetch_stream) (void)hipStreamDestroy(s->fetch_stream);
+    if (s->pin_desc) (void)hipHostFree(s->pin_desc);
+    if (s->pin) (void)hipHostFree(s->pin);
     delete s;
 }
 
@@ -466,27 +500,29 @@ int submit_trace(smp_sampler_t* s, const smp_event_t* ev, uint64_t n, const smp_
     return SMP_OK;
 }
 
-// The kernels of one launch, in stream order on r.stream, with the timing
-// events between passes that k asks for (captured into a graph when called
+// The kernels of one launch, in stream order on r.stream, with the start
+// times of the passes that k asks for (captured into a graph when called
 // between hipStreamBeginCapture and hipStreamEndCapture, which is done only
-// for launches without such events).
+// for launches without such times).
 static hipError_t issue_launch(RunSlot& r, const LaunchKey& k) {
     hipError_t e = hipSuccess;
     auto ok = [&](hipError_t x) {
         if (e == hipSuccess) e = x;
         return e == hipSuccess;
     };
-    auto record = [&](hipEvent_t ev) { return hipEventRecord(ev, r.stream); };
+    // where pass p's kernel (p = NPASS: the one after the last pass) writes its start, if this launch times it
+    auto ts = [&](int p) { return (k.ev_mask >> p) & 1u ? r.host_ts_dev + p : nullptr; };
     const int cnt = (int)k.cnt;
     if (!ok(launch_clear(r.dev_desc, cnt, k.zero, r.dev_ticket, r.stream))) return e;
     for (int p = 0; p < NPASS; ++p) {
-        if ((k.ev_mask >> p) & 1u && !ok(record(r.e_pass[p]))) return e;
         const int lim = p == 2 ? (int)k.chain_grid : (int)k.emit_grid;
-        if (p == 1 && k.tmap && !ok(launch_tmap(r.dev_desc, cnt, k.tile, r.dev_ticket, r.stream))) return e;
-        if (!ok(launch_pass(p, r.dev_desc, cnt, k.seg, k.tile, r.dev_ticket, lim, r.stream))) return e;
+        const bool maps = p == 1 && k.tmap && k.tile;
+        if (maps && !ok(launch_tmap(r.dev_desc, cnt, k.tile, r.dev_ticket, ts(p), r.stream))) return e;
+        if (!ok(launch_pass(p, r.dev_desc, cnt, k.seg, k.tile, r.dev_ticket, lim, maps ? nullptr : ts(p), r.stream)))
+            return e;
     }
-    if ((k.ev_mask >> NPASS) & 1u && !ok(record(r.e_pass[NPASS]))) return e;
-    ok(launch_finish(r.dev_desc, cnt, k.blk, k.lines, r.dev_ticket, (int)k.track_grid, r.host_scal_dev, r.stream));
+    ok(launch_finish(r.dev_desc, cnt, k.blk, k.lines, r.dev_ticket, (int)k.track_grid, r.host_scal_dev, ts(NPASS),
+                     r.stream));
     return e;
 }
 
@@ -641,7 +677,6 @@ int run(smp_sampler_t* s, int blocking) {
             memcpy(r.last_desc, r.host_desc, sizeof(Desc) * cnt);
             r.last_cnt = cnt;
         }
-        // an event between two kernels costs a few microseconds of idle GPU
         r.ev_mask = s->pass_events;
         // A shape this slot launched before is replayed as a HIP graph (the
         // kernels read the descriptors uploaded above; no memset nodes: the
@@ -716,13 +751,36 @@ int fetch_profile(smp_sampler_t* s, uint64_t trace_id, smp_profile_sizes_t* size
     sizes->status = status;
     if (!out) return SMP_OK;
     const uint64_t L = t.params.num_lines;
-    if (out->samples && sc.K)
-        HIPCHK(hipMemcpy(out->samples, base + t.lay.samples, sizeof(Sample) * sc.K, hipMemcpyDeviceToHost));
-    if (out->tracked && sc.H)
-        HIPCHK(hipMemcpy(out->tracked, base + t.lay.tracked, sizeof(Tracked) * sc.H, hipMemcpyDeviceToHost));
-    if (out->hist) HIPCHK(hipMemcpy(out->hist, base + t.lay.hist, 8 * H_COUNT * L, hipMemcpyDeviceToHost));
-    if (out->leak) HIPCHK(hipMemcpy(out->leak, base + t.lay.leak, 8 * 4 * L, hipMemcpyDeviceToHost));
-    if (out->gates) HIPCHK(hipMemcpy(out->gates, base + t.lay.gates, 2 * L, hipMemcpyDeviceToHost));
+    const bool lines = out->hist || out->leak || out->gates;
+    const uint64_t bs = out->samples ? sizeof(Sample) * sc.K : 0, bt = out->tracked ? sizeof(Tracked) * sc.H : 0;
+    const uint64_t bl = lines ? align_up(t.lay.gates + 2 * L - t.lay.hist, 8) : 0;
+    if (bs + bt + bl == 0) {
+    } else if (bs + bt + bl <= FETCH_STAGE) {
+        const CopyOut c{{(const uint64_t*)(base + t.lay.samples), (const uint64_t*)(base + t.lay.tracked),
+                         (const uint64_t*)(base + t.lay.hist)},
+                        {bs / 8, bt / 8, bl / 8},
+                        {0, bs / 8, (bs + bt) / 8}};
+        HIPCHK(launch_copy_out(c, s->stage_dev, s->fetch_stream));
+        HIPCHK(hipStreamSynchronize(s->fetch_stream));
+        if (bs) memcpy(out->samples, s->stage, bs);
+        if (bt) memcpy(out->tracked, s->stage + bs, bt);
+        const uint8_t* per_line = s->stage + bs + bt;
+        if (out->hist) memcpy(out->hist, per_line, 8 * H_COUNT * L);
+        if (out->leak) memcpy(out->leak, per_line + (t.lay.leak - t.lay.hist), 8 * 4 * L);
+        if (out->gates) memcpy(out->gates, per_line + (t.lay.gates - t.lay.hist), 2 * L);
+    } else {
+        auto copy = [&](void* dst, uint64_t off, uint64_t bytes) {
+            return !dst || !bytes
+                       ? hipSuccess
+                       : hipMemcpyAsync(dst, base + off, bytes, hipMemcpyDeviceToHost, s->fetch_stream);
+        };
+        HIPCHK(copy(out->samples, t.lay.samples, bs));
+        HIPCHK(copy(out->tracked, t.lay.tracked, bt));
+        HIPCHK(copy(out->hist, t.lay.hist, 8 * H_COUNT * L));
+        HIPCHK(copy(out->leak, t.lay.leak, 8 * 4 * L));
+        HIPCHK(copy(out->gates, t.lay.gates, 2 * L));
+        HIPCHK(hipStreamSynchronize(s->fetch_stream));
+    }
     out->final_F = sc.final_F;
     out->peak_F = sc.peak_F;
     out->peak_sampled_F = sc.peak_S;

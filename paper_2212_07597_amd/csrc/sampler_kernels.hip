@@ -127,6 +127,16 @@ __device__ __forceinline__ int find_trace_tile(const Desc* desc, int ntraces, ui
     return lo;
 }
 
+// -------------------------------------------------------------- time stamps
+
+// The device clock when a pass starts, for the host's pass timing (ts: the
+// word in pinned host memory, null when the pass is not timed).  Kernels of a
+// stream do not overlap, so a pass lasts from its own stamp to the next
+// one's.  A HIP event between two kernels left the GPU idle for 5.7 us.
+__device__ __forceinline__ void stamp(uint64_t* ts) {
+    if (ts && blockIdx.x == 0 && threadIdx.x == 0) *gp(ts) = (uint64_t)wall_clock64();
+}
+
 // ------------------------------------------------------------ event records
 
 // One decoded record (24 bytes: delta i64, ptr u32, line u32, flags u8).
@@ -888,8 +898,9 @@ __device__ __forceinline__ void summarize_segment(const Desc& D, uint64_t g, int
 // than a grid-stride loop: the hardware starts a new wave's loads while
 // others compute).
 __global__ __launch_bounds__(BLOCK) void k_summarize(const Desc* __restrict__ desc, int ntraces,
-                                                     uint64_t nseg_total) {
+                                                     uint64_t nseg_total, uint64_t* ts) {
     __shared__ int64_t lF[WAVES][SEG];
+    stamp(ts);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
     const uint64_t g = (uint64_t)blockIdx.x * WAVES + wv;
     if (g >= nseg_total) return;
@@ -1237,7 +1248,9 @@ __device__ void chain_maps(const Desc& D, unsigned long long* ctl) {
 
 // One wave per tile (grid: every tile of the launch; tiles of traces without
 // maps return at once).
-__global__ __launch_bounds__(64) void k_tmap(const Desc* __restrict__ desc, int ntraces, unsigned long long* ctl) {
+__global__ __launch_bounds__(64) void k_tmap(const Desc* __restrict__ desc, int ntraces, unsigned long long* ctl,
+                                             uint64_t* ts) {
+    stamp(ts);
     __shared__ int64_t cx[TM_CAP];       // live chains: reference (tile coordinates)
     __shared__ uint16_t cr[TM_CAP];      // and the root source of their set
     __shared__ uint16_t par[TM_SRC];     // union-find parent of each source
@@ -2057,7 +2070,8 @@ __device__ __forceinline__ int32_t block_refs(const Desc& D, int64_t j0, int nb,
 // costs the walker only a pass over LDS.  Tiles of several SIM segments whose
 // blocks qualify take block maps (above) instead of the walk.
 __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void k_resolve(const Desc* __restrict__ desc, int ntraces, uint64_t ntile_total,
-                                                  unsigned long long* ctl) {
+                                                  unsigned long long* ctl, uint64_t* ts_) {
+    stamp(ts_);
     __shared__ unsigned long long s_tk;
     __shared__ int64_t w_sum[3][TWAVES];
     __shared__ int64_t s_pre[3];
@@ -2651,7 +2665,9 @@ __device__ __forceinline__ void load_head(const Desc& D, int64_t j, ChainHead& h
 // One wave per segment (grid-stride): follow the chain from the segment's
 // entry offset; record its samples, count, best growth sample and the Python
 // footprint at its last sample.  Copy and timer events are counted here.
-__global__ __launch_bounds__(BLOCK) void k_chain(const Desc* __restrict__ desc, int ntraces, uint64_t nseg_total) {
+__global__ __launch_bounds__(BLOCK) void k_chain(const Desc* __restrict__ desc, int ntraces, uint64_t nseg_total,
+                                                 uint64_t* ts) {
+    stamp(ts);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
     const int l = lane_id();
     int cur_t = 0;
@@ -2856,7 +2872,8 @@ __device__ __forceinline__ BItem bcombine(const BItem& a, const BItem& b) {
 
 // One workgroup per tile (ticket order): the state before every segment.
 __global__ __launch_bounds__(TILE) void k_bscan(const Desc* __restrict__ desc, int ntraces, uint64_t ntile_total,
-                                                unsigned long long* ctl) {
+                                                unsigned long long* ctl, uint64_t* ts_) {
+    stamp(ts_);
     __shared__ unsigned long long s_tk;
     __shared__ int64_t w_cnt[TWAVES], w_val[TWAVES], w_ls[TWAVES];
     __shared__ uint32_t w_idx[TWAVES], w_ptr[TWAVES];
@@ -3215,7 +3232,8 @@ __device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, cons
 }
 
 __global__ __launch_bounds__(EMIT_BLOCK) __attribute__((amdgpu_waves_per_eu(5))) void k_emit(
-    const Desc* __restrict__ desc, int ntraces, uint64_t nseg_total) {
+    const Desc* __restrict__ desc, int ntraces, uint64_t nseg_total, uint64_t* ts) {
+    stamp(ts);
     __shared__ HistCache<EMIT_SLOTS> hc;
     __shared__ Sample stage[EMIT_WAVES][STAGE];
     hist_init(hc);
@@ -3355,7 +3373,8 @@ __device__ bool count_lookback(const uint64_t* st, int64_t b, uint64_t& excl, un
 // here; the last one of a trace (unresolved unless RESOLVE_AT_END) is taken
 // back out by k_finish.
 __global__ __launch_bounds__(256) void k_track(const Desc* __restrict__ desc, int ntraces, uint64_t nblk_total,
-                                               unsigned long long* ctl) {
+                                               unsigned long long* ctl, uint64_t* ts) {
+    stamp(ts);
     __shared__ HistCache<TRACK_SLOTS> hc;
     __shared__ uint64_t s_excl;
     __shared__ uint64_t w_cnt[4];
@@ -3485,7 +3504,9 @@ __device__ int64_t gcd64(int64_t x, int64_t y) {
 // out of that line's frees.  Threads below 8 x ntraces also gather every
 // trace's scalars (final from here on) into one array, which may live in
 // pinned host memory (the host reads it once the launch has completed).
-__global__ void k_finish(const Desc* __restrict__ desc, int ntraces, uint64_t total_lines, Scalars* gather) {
+__global__ void k_finish(const Desc* __restrict__ desc, int ntraces, uint64_t total_lines, Scalars* gather,
+                         uint64_t* ts) {
+    stamp(ts);
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < (uint64_t)ntraces * 8) {
         const uint64_t t = i >> 3, w = i & 7;  // 8 words per Scalars
@@ -3538,6 +3559,19 @@ __global__ void k_finish(const Desc* __restrict__ desc, int ntraces, uint64_t to
     gates[D.L + line] = g2;
 }
 
+// ---------------------------------------------------------------- copy out
+
+// A finished trace's results into pinned host memory, up to three ranges one
+// behind another (offsets and lengths in 8-byte words): one launch and one
+// wait in place of a blocking copy per array.
+__global__ __launch_bounds__(256) void k_copy_out(CopyOut c, uint64_t* dst) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+        for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < c.words[r]; i += stride)
+            gp(dst)[c.at[r] + i] = gp(c.src[r])[i];
+}
+
 // ------------------------------------------------------------ launchers
 
 static int occupancy_grid(const void* fn, int block) {
@@ -3553,32 +3587,41 @@ int emit_grid_limit() { return occupancy_grid((const void*)k_emit, EMIT_BLOCK); 
 // workgroups of k_track the device holds at once (its look-back needs all of them resident)
 int track_grid_limit() { return occupancy_grid((const void*)k_track, 256); }
 
+hipError_t launch_copy_out(const CopyOut& c, uint64_t* dst, hipStream_t s) {
+    uint64_t most = 1;
+    for (uint64_t w : c.words) most = w > most ? w : most;
+    const uint64_t blocks = (most + 511) / 512;
+    k_copy_out<<<dim3((unsigned)(blocks < 256 ? blocks : 256)), dim3(256), 0, s>>>(c, dst);
+    return hipGetLastError();
+}
+
 hipError_t launch_clear(const Desc* desc, int ntraces, uint64_t total_bytes, unsigned long long* ctl, hipStream_t s) {
     const uint64_t blocks = (total_bytes + (1ull << 16) - 1) >> 16;
     k_clear<<<dim3((unsigned)(blocks ? blocks : 1)), dim3(256), 0, s>>>(desc, ntraces, total_bytes, ctl);
     return hipGetLastError();
 }
 
-hipError_t launch_tmap(const Desc* desc, int ntraces, uint64_t ntile_total, unsigned long long* ctl, hipStream_t s) {
+hipError_t launch_tmap(const Desc* desc, int ntraces, uint64_t ntile_total, unsigned long long* ctl, uint64_t* ts,
+                       hipStream_t s) {
     if (ntile_total == 0) return hipSuccess;
-    k_tmap<<<dim3((unsigned)ntile_total), dim3(64), 0, s>>>(desc, ntraces, ctl);
+    k_tmap<<<dim3((unsigned)ntile_total), dim3(64), 0, s>>>(desc, ntraces, ctl, ts);
     return hipGetLastError();
 }
 
 hipError_t launch_pass(int pass, const Desc* desc, int ntraces, uint64_t nseg_total, uint64_t ntile_total,
-                       unsigned long long* ctl, int grid_limit, hipStream_t s) {
+                       unsigned long long* ctl, int grid_limit, uint64_t* ts, hipStream_t s) {
     if (nseg_total == 0) return hipSuccess;
     const uint64_t wgs = (nseg_total + WAVES - 1) / WAVES;
     const unsigned pgrid = (unsigned)(wgs < (uint64_t)grid_limit ? wgs : (uint64_t)grid_limit);
     switch (pass) {
-        case 0: k_summarize<<<dim3((unsigned)wgs), dim3(BLOCK), 0, s>>>(desc, ntraces, nseg_total); break;
-        case 1: k_resolve<<<dim3((unsigned)ntile_total), dim3(TILE), 0, s>>>(desc, ntraces, ntile_total, ctl); break;
-        case 2: k_chain<<<dim3(pgrid), dim3(BLOCK), 0, s>>>(desc, ntraces, nseg_total); break;
-        case 3: k_bscan<<<dim3((unsigned)ntile_total), dim3(TILE), 0, s>>>(desc, ntraces, ntile_total, ctl); break;
+        case 0: k_summarize<<<dim3((unsigned)wgs), dim3(BLOCK), 0, s>>>(desc, ntraces, nseg_total, ts); break;
+        case 1: k_resolve<<<dim3((unsigned)ntile_total), dim3(TILE), 0, s>>>(desc, ntraces, ntile_total, ctl, ts); break;
+        case 2: k_chain<<<dim3(pgrid), dim3(BLOCK), 0, s>>>(desc, ntraces, nseg_total, ts); break;
+        case 3: k_bscan<<<dim3((unsigned)ntile_total), dim3(TILE), 0, s>>>(desc, ntraces, ntile_total, ctl, ts); break;
         default: {
             const uint64_t ewgs = (nseg_total + EMIT_WAVES - 1) / EMIT_WAVES;
             const unsigned egrid = (unsigned)(ewgs < (uint64_t)grid_limit ? ewgs : (uint64_t)grid_limit);
-            k_emit<<<dim3(egrid), dim3(EMIT_BLOCK), 0, s>>>(desc, ntraces, nseg_total);
+            k_emit<<<dim3(egrid), dim3(EMIT_BLOCK), 0, s>>>(desc, ntraces, nseg_total, ts);
             break;
         }
     }
@@ -3586,13 +3629,14 @@ hipError_t launch_pass(int pass, const Desc* desc, int ntraces, uint64_t nseg_to
 }
 
 hipError_t launch_finish(const Desc* desc, int ntraces, uint64_t nblk_total, uint64_t total_lines,
-                         unsigned long long* ctl, int track_grid, Scalars* gather, hipStream_t s) {
+                         unsigned long long* ctl, int track_grid, Scalars* gather, uint64_t* ts, hipStream_t s) {
     if (nblk_total) {
         const unsigned g = (unsigned)(nblk_total < (uint64_t)track_grid ? nblk_total : (uint64_t)track_grid);
-        k_track<<<dim3(g), dim3(256), 0, s>>>(desc, ntraces, nblk_total, ctl);
+        k_track<<<dim3(g), dim3(256), 0, s>>>(desc, ntraces, nblk_total, ctl, ts);
+        ts = nullptr;
     }
     const uint64_t items = total_lines > (uint64_t)ntraces * 8 ? total_lines : (uint64_t)ntraces * 8;
-    k_finish<<<dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s>>>(desc, ntraces, total_lines, gather);
+    k_finish<<<dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s>>>(desc, ntraces, total_lines, gather, ts);
     return hipGetLastError();
 }
 
