@@ -285,7 +285,7 @@ SMP_API int sampler_last_counters(smp_sampler_t *s, uint64_t *out32);
  *                all entries (section 3.2), built for all tiles at once
  *                before the resolve pass, so that tile entries follow by one
  *                lookup per tile instead of a walk per tile (0 = the default,
- *                64; 0xFFFFFFFF = never)
+ *                8; 0xFFFFFFFF = never)
  * sampler_set_tuning returns SMP_EINVAL for values out of range;
  * sampler_get_tuning reports the current ones with the defaults resolved. */
 typedef struct {

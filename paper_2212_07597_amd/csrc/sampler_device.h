@@ -22,6 +22,7 @@ constexpr int TRACK_SLOTS = 64;          // and tracked-list pass (mallocs, free
 constexpr int NCNT = 12;                 // counters cached per slot
 constexpr int CHAIN_CAP_MAX = 64;        // chains the all-entry analysis can follow (one per lane)
 constexpr uint64_t TILE_MAP_BYTES = 32768;  // map area per tile (in the tracked-list area)
+constexpr uint64_t TILE_MAP_ROOM = 163840;  // with the scratch of a tile's blocks
 
 constexpr int64_t MAX_ABS_DELTA = (int64_t)1 << 52;
 constexpr int64_t MAX_ABS_F = (int64_t)1 << 61;
@@ -97,9 +98,9 @@ struct Scalars {
     uint64_t K;
     uint64_t H;
     uint32_t err;      // bit 0: malformed event, bit 1: overflow, bits 2-3: internal fault
-    uint32_t pad;
-    uint64_t tmap_done;  // tiles whose tile-map wave has finished (the last one chains them)
-    uint64_t reserved;
+    uint32_t pad;        // tile maps: the tile the chain stands at
+    uint64_t tmap_done;  // tiles whose map is done
+    uint64_t reserved;   // 1 while a wave chains tiles
 };
 
 // Per-trace descriptor, built by the host for every launch.

@@ -1054,14 +1054,43 @@ __device__ __forceinline__ uint64_t range_mask(int w, int lo, int hi) {
     return ma & mb;
 }
 
+// The first node of a segment at least T from each lane's reference xr (a
+// lane that crosses nowhere gets some node): f holds the prefixes, lane g of
+// cgx and cgn the largest and smallest prefix up to the end of the eight-node
+// group g: a binary search over the groups, then the nodes of one.  (Two
+// levels of eight groups with their reads in flight together: 8 % slower.)
+__device__ __forceinline__ int first_samples(const int32_t* f, int32_t cgx, int32_t cgn, int32_t T, int32_t xr,
+                                             int32_t& v) {
+    const int32_t hi = xr + T, lo = xr - T;
+    int g = 0;
+#pragma unroll
+    for (int d = 32; d; d >>= 1) {
+        const int32_t mx = shfl32(cgx, g + d - 1), mn = shfl32(cgn, g + d - 1);
+        g += mx >= hi || mn <= lo ? 0 : d;
+    }
+    g &= 63;
+    const v4i32 a = *(const v4i32*)&f[8 * g], b = *(const v4i32*)&f[8 * g + 4];
+    const uint32_t span = (uint32_t)(2 * T - 1);
+    int e = 7;
+    v = b[3];
+#pragma unroll
+    for (int i = 6; i >= 0; --i) {
+        const int32_t y = i < 4 ? a[i & 3] : b[i & 3];
+        const bool c = (uint32_t)(y + (T - 1) - xr) >= span;
+        e = c ? i : e;
+        v = c ? y : v;
+    }
+    return 8 * g + e;
+}
+
 // ------------------------------------------------------------ tile maps
 //
 // A tile whose segments each move less than T (every SIM map holds at least
 // T entries in its no-sample interval) lets an entry sample at most once per
-// segment.  For such a tile the chain map over all entry offsets of
-// the whole tile is computed by one wave, segment by segment, before the
-// resolve pass (section 3.2's rule, restated over entries as in the segment
-// analysis):
+// segment.  For such a tile the chain map over all entry offsets of the whole
+// tile is computed before the resolve pass (section 3.2's rule, restated over
+// entries as in the segment analysis): each of eight waves follows a block of
+// 64 segments, segment by segment, and the eight maps are composed:
 //  * entries that have not sampled yet form one interval U, which shrinks as
 //    the tile's running maximum and minimum footprint grow apart;
 //  * at each new running maximum (minimum) node while U is not empty, the
@@ -1075,16 +1104,16 @@ __device__ __forceinline__ uint64_t range_mask(int w, int lo, int hi) {
 // Source intervals started at maxima lie below U and grow upward in start
 // order; those started at minima lie above it and grow downward.  Runs of
 // consecutive sources that end at the same reference are written as (bound,
-// exit) pairs, so that the tile's exit for any entry is one search.  The
-// last of a trace's tile waves to finish then chains the trace's tile entries
-// through the maps in tile order and publishes every tile's exit, so that the
-// resolve pass no longer waits for the previous tile's walk.  A tile that
+// exit) pairs, so that the tile's exit for any entry is one search.  Waves
+// that have finished a tile chain the trace's tile entries through the maps in
+// tile order and publish every tile's exit, so that the resolve pass does not
+// wait for the previous tile's walk.  A tile that
 // does not qualify, or whose chains or runs exceed the capacities below, gets
 // no map; the resolve pass chains the tiles from it on, by a map lookup where
 // a tile has one and by its walk where not.
 
-constexpr int TM_CAP = 1024;   // chains followed at once
-constexpr int TM_SRC = 2048;   // source intervals per tile
+constexpr int TM_CAP = 1024;   // chains followed at once (64-bit path)
+constexpr int TM_SRC = 2048;   // source intervals per tile (64-bit path)
 constexpr int TM_SIDE = 128;   // runs per side (below and above U)
 constexpr int64_t TM_WORDS = (int64_t)(TILE_MAP_BYTES / 8);
 // Run r of side s (0: below U, 1: above) has its bound at run_word(s, 0, r)
@@ -1173,31 +1202,31 @@ __device__ __forceinline__ int64_t map_exit64(int64_t e, uint64_t vu, uint64_t v
     return u ? xu : (d ? xd : e - tF);
 }
 
-// The tile entries of a trace, chained through the maps in tile order by one
-// wave (tile 0's entry is 0): each tile's exit is published as the word the
-// resolve pass waits for.  It stops at the first tile without a map.  Tiles
-// are taken TC_CB at a time, the next ones' words loading while these are
-// looked up.
+// The tile entries of a trace, chained through the maps of tiles t0 to nt - 1
+// by one wave: each tile's exit is published as the word the resolve pass
+// waits for.  It stops at the first tile without a map; returns the tiles
+// chained.  Tiles are taken TC_CB at a time, the next ones' words loading
+// while these are looked up.
 constexpr int TC_CB = 8;
-__device__ void chain_maps(const Desc& D, unsigned long long* ctl) {
+__device__ int chain_maps(const Desc& D, int t0, int nt, unsigned long long* ctl) {
     const int l = lane_id();
-    const int nt = __builtin_amdgcn_readfirstlane((int)D.ntile);
-    const StatusView ts{D.tstat, (int64_t)nt};
+    const StatusView ts{D.tstat, (int64_t)D.ntile};
     // lane l: runs l of both sides (bound, exit below U; bound, exit above);
     // lanes 0-3: the header
-    auto load = [&](int t0, int64_t (&w)[TC_CB][4], int64_t (&h)[TC_CB]) {
+    auto load = [&](int at, int64_t (&w)[TC_CB][4], int64_t (&h)[TC_CB]) {
 #pragma unroll
         for (int b = 0; b < TC_CB; ++b) {
-            const SMP_GLOBAL int64_t* m = tile_map(D, t0 + b < nt ? t0 + b : nt - 1);
+            const SMP_GLOBAL int64_t* m = tile_map(D, at + b < nt ? at + b : nt - 1);
 #pragma unroll
             for (int q = 0; q < 4; ++q) w[b][q] = m[4 * l + q];
             h[b] = m[TM_HDR + (l & 3)];
         }
     };
     int64_t nw[TC_CB][4], nh[TC_CB];
-    load(0, nw, nh);
-    int64_t e = 0;
-    int t = 0;
+    load(t0, nw, nh);
+    // tile 0's entry is 0, every other's the exit published before it
+    int64_t e = t0 ? unpack(readlaneu64(ld_status(ts.at(W_XF, t0 - 1)), 0)) : 0;
+    int t = t0;
     for (; t < nt;) {
         int64_t cw[TC_CB][4], ch[TC_CB];
 #pragma unroll
@@ -1243,48 +1272,82 @@ __device__ void chain_maps(const Desc& D, unsigned long long* ctl) {
         t += done;
         if (done < nb) break;  // a tile without a map
     }
-    if (l == 0 && t > 0) g_add((uint64_t*)&ctl[6], (uint64_t)t);
+    if (l == 0 && t > t0) g_add((uint64_t*)&ctl[6], (uint64_t)(t - t0));
+    return t - t0;
 }
 
-// One wave per tile (grid: every tile of the launch; tiles of traces without
-// maps return at once).
-__global__ __launch_bounds__(64) void k_tmap(const Desc* __restrict__ desc, int ntraces, unsigned long long* ctl,
-                                             uint64_t* ts) {
-    stamp(ts);
-    __shared__ int64_t cx[TM_CAP];       // live chains: reference (tile coordinates)
-    __shared__ uint16_t cr[TM_CAP];      // and the root source of their set
-    __shared__ uint16_t par[TM_SRC];     // union-find parent of each source
+// Chain what can be chained, by the wave that has just finished a tile's map:
+// tiles are marked as they are done (D.blk, which the tracked-list pass finds
+// cleared again), and whichever wave finds the chain free (Scalars::reserved)
+// takes it on from where it stands (Scalars::pad) over the marked tiles.  The
+// last tile's wave waits for the chain and finishes it.  So the chain runs
+// beside the builds (5e8 events, 1,908 tiles: 0.7 ms of it), not after them.
+__device__ void chain_done_tiles(const Desc& D, int64_t k, unsigned long long* ctl) {
+    const int l = lane_id();
+    const int nt = __builtin_amdgcn_readfirstlane((int)D.ntile);
+    // the map's words were stored through to memory: complete after this
+    // fence, as the mark is before the tile is counted
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (l == 0) st_status(D.blk + k, 1);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    uint64_t done = 0;
+    if (l == 0) done = g_add_rtn(&D.scal->tmap_done, 1ull);
+    const bool last = readlaneu64(done, 0) == (uint64_t)nt - 1;
+    Spin sp;
+    for (;;) {
+        uint64_t held = 0;
+        if (l == 0)
+            held = __hip_atomic_exchange(gp(&D.scal->reserved), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!readlaneu64(held, 0)) break;
+        if (!last || spin_abort(ctl, sp)) return;
+    }
+    int pos = readlane32((int)__hip_atomic_load(gp(&D.scal->pad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0);
+    while (pos < nt) {
+        const int t = pos + l;
+        const uint64_t ready = ballot(t < nt && ld_status(D.blk + (t < nt ? t : 0)) != 0);
+        const int n = ~ready ? ctz64(~ready) : 64;
+        if (!n) break;
+        // drop stale copies of the tiles' words before they are read
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const int c = chain_maps(D, pos, pos + n, ctl);
+        pos = c < n ? nt : pos + n;  // (a tile without a map ends the chain)
+    }
+    if (last) {
+        for (int i = l; i < nt; i += 64) st_status(D.blk + i, 0);
+        return;
+    }
+    if (l == 0) __hip_atomic_store(gp(&D.scal->pad), (uint32_t)pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the exits and the position are in memory before the chain is free
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (l == 0) __hip_atomic_store(gp(&D.scal->reserved), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The map of a tile past the 32-bit range, by one wave over all its segments
+// (64-bit references, prefixes loaded as they are used).  Returns the cause
+// if it fails, 0 if the runs are written.
+struct TmapWide {
+    int64_t cx[TM_CAP];       // live chains: reference (tile coordinates)
+    uint16_t cr[TM_CAP];      // and the root source of their set
+    uint16_t par[TM_SRC];     // union-find parent of each source
     // per segment: its prefixes, and per node the chain that sampled there
     // first (see claim below); at the end: the live chain of each root
-    __shared__ int64_t lds_u[(SEG * 8 + SEG * 4 > TM_SRC * 2 ? SEG * 8 + SEG * 4 : TM_SRC * 2) / 8];
-    int64_t* fl = lds_u;
-    uint32_t* claim = (uint32_t*)(lds_u + SEG);
-    uint16_t* cidx = (uint16_t*)lds_u;
+    int64_t u[(SEG * 8 + SEG * 4 > TM_SRC * 2 ? SEG * 8 + SEG * 4 : TM_SRC * 2) / 8];
+};
+__device__ int tmap_wide(const Desc& D, int64_t k, int nval, TmapWide& W, SMP_GLOBAL int64_t* map) {
+    int64_t (&cx)[TM_CAP] = W.cx;
+    uint16_t (&cr)[TM_CAP] = W.cr;
+    uint16_t (&par)[TM_SRC] = W.par;
+    int64_t* fl = W.u;
+    uint32_t* claim = (uint32_t*)(W.u + SEG);
+    uint16_t* cidx = (uint16_t*)W.u;
     const int l = lane_id();
-    const uint64_t tk = blockIdx.x;
-    const Desc& D = desc[find_trace_tile(desc, ntraces, tk)];
-    if (!D.tmap) return;
-    const int64_t k = (int64_t)(tk - D.tile_begin);
     const int64_t ns = (int64_t)D.nseg;
-    const int nval = (int)((ns - k * TILE) < TILE ? (ns - k * TILE) : TILE);
     const int64_t T = D.T;
-    SMP_GLOBAL int64_t* map = tile_map(D, k);
     SMP_GLOBAL uint8_t* sside = (SMP_GLOBAL uint8_t*)(map + TM_SD);
     const SMP_GLOBAL int64_t* sp = gp(D.seg) + k * TILE;
-    // every segment SIM, with a no-sample interval of at least T entries
-    // (then max - min < T over its prefixes and the entry)
-    bool ok = prefixes_kept(D), fit = true;  // fit: every segment keeps 32-bit prefixes
-    for (int g = 0; g < nval && ok; g += 64) {
-        const int s = g + l;
-        const bool v = s < nval;
-        const int64_t lo = v ? sp[SP_LO * ns + s] : 0, hi = v ? sp[SP_HI * ns + s] : 0;
-        const int64_t fl_ = v ? sp[SP_FLG * ns + s] : 0;
-        if (ballot(v && ((fl_ & 3) != MAP_SIM || hi < lo || hi - lo < T - 1))) ok = false;
-        if (ballot(v && !(fl_ & FLG_FIT))) fit = false;
-    }
     for (int i = l; i < SEG; i += 64) claim[i] = 0;
     int nch = 0, nsrc = 0;
-    int fail = ok ? 0 : TMF_QUALIFY;  // cause, 0 while the map holds
+    int fail = 0;  // cause, 0 while the map holds
     int64_t Umax = 0, Umin = 0, carry = 0;  // running extremes (from the tile start), footprint change so far
     // segments g..g+63, one per lane: offset, no-sample bounds and extremes in tile coordinates
     int64_t gR = 0, gL = 0, gH = 0, gX = 0, gN = 0;
@@ -1452,26 +1515,11 @@ __global__ __launch_bounds__(64) void k_tmap(const Desc* __restrict__ desc, int 
         Umax = Sx > Umax ? Sx : Umax;
         Umin = Sn < Umin ? Sn : Umin;
     };
-    // the next segment's prefixes load while one is processed (into fn,
-    // copied out at the start of each step: the only loads then in flight
-    // are the ones the copy needs, issued a whole step earlier)
     const int64_t j0 = k * TILE;
-    if (fit) {
-        int32_t fn[NW];
-        if (!fail) load_kept32(D, j0, fn);
-        for (int s = 0; s < nval && !fail; ++s) {
-            int64_t f[NW];
-#pragma unroll
-            for (int w = 0; w < NW; ++w) f[w] = fn[w];
-            load_kept32(D, j0 + (s + 1 < nval ? s + 1 : s), fn);
-            step(s, f);
-        }
-    } else {  // (a segment that moves 2^30 or more: loaded as it is used)
-        for (int s = 0; s < nval && !fail; ++s) {
-            int64_t f[NW];
-            load_kept(D, j0 + s, (sp[SP_FLG * ns + s] & FLG_FIT) != 0, f);
-            step(s, f);
-        }
+    for (int s = 0; s < nval && !fail; ++s) {
+        int64_t f[NW];
+        load_kept(D, j0 + s, (sp[SP_FLG * ns + s] & FLG_FIT) != 0, f);
+        step(s, f);
     }
     // runs: consecutive sources of one side that end at the same reference
     int nup = 0, ndn = 0;
@@ -1530,21 +1578,443 @@ __global__ __launch_bounds__(64) void k_tmap(const Desc* __restrict__ desc, int 
             st_map(map + TM_HDR + 3, tF);
         }
     }
+    return fail;
+}
+
+// A 32-bit tile: eight waves, each following the chains of its 64 segments,
+// then the eight maps composed.  Chains that stop in a segment are searched
+// side by side (64 at a time).  Bound: the serial steps of 64 segments (one
+// wave over all 512 took 0.88 ms whatever the number of tiles).
+constexpr int TS_SRC = 2048;  // sources per block, pieces per tile
+constexpr int TS_CAP = 1088;  // chains followed at once
+constexpr int TS_UNROLL = 4;
+constexpr int TS_FRESH = 43;  // segments with new extremes a tile may have
+constexpr int32_t TS_DEAD = INT32_MIN;
+struct TmapBuild {
+    int32_t cx[TS_CAP];       // live chains: reference (block coordinates), TS_DEAD once merged
+    uint16_t cr[TS_CAP];      // and the root source of their set
+    uint16_t par[TS_SRC];     // union-find parent of each source
+    union {
+        struct {
+            int32_t f[SEG];       // the current segment's prefixes
+            uint32_t claim[SEG];  // the chain that sampled at each node: (segment + 1) << 16 | root
+            uint16_t lst[TS_CAP]; // the chains that stop in it
+        } s;
+        uint16_t cidx[TS_SRC];    // at the end: the live chain of each root
+    } u;
+};
+// A map as runs: those below the unsampled interval from the front (bounds
+// growing: the largest entry of each), those above it from the back (bounds
+// falling: the smallest).
+struct TmapRuns {
+    int32_t b[TS_SRC], e[TS_SRC];
+};
+union alignas(16) TmapLds {
+    TmapBuild build;
+    TmapRuns runs;
+};
+struct TmapBlock {
+    int nup, ndn;
+    int32_t lo, hi;  // unsampled entries (none: lo > hi)
+    int64_t rend;    // the block's footprint change
+    int fail;
+};
+// Scratch of block b of tile k (sources' bounds and exits), behind the tiles' maps.
+__device__ __forceinline__ SMP_GLOBAL int32_t* tmap_scratch(const Desc& D, int64_t k, int b) {
+    return (SMP_GLOBAL int32_t*)((SMP_GLOBAL uint8_t*)gp((uint8_t*)D.tracked) + (uint64_t)D.ntile * TILE_MAP_BYTES) +
+           (k * TWAVES + b) * (2 * TS_SRC);
+}
+static_assert(TILE_MAP_BYTES + TWAVES * 2 * TS_SRC * 4 <= TILE_MAP_ROOM, "scratch of a tile");
+
+// Runs of one side among 64 lanes in order (mine: lanes of that side, ex:
+// their exits, bnd: their bounds): store(run, which, value) writes a run's
+// bound (0) and exit (1).  cnt: runs so far, last: the exit of the latest.
+template <class F>
+__device__ __forceinline__ void add_runs(bool mine, int64_t ex, int64_t bnd, int& cnt, int64_t& last, F store) {
+    const uint64_t sm = ballot(mine);
+    if (!sm) return;
+    // the previous one of this side: an earlier lane, else the carried one
+    const uint64_t before = sm & lanemask_lt();
+    const int64_t pe = shfl64(ex, before ? top64(before) : 0);
+    const bool start = mine && ((before == 0 && cnt == 0) || ex != (before ? pe : last));
+    const uint64_t stm = ballot(start), le = lanemask_lt() | (1ull << lane_id());
+    const int run = cnt + __popcll(stm & le) - 1;
+    // one whose next of this side starts a new run, or that is the last of
+    // these lanes, writes the bound (a later call may still extend its run)
+    const uint64_t after = sm & ~le;
+    const bool ends = mine && (!after || ((stm >> ctz64(after)) & 1));
+    if (start) store(run, 1, ex);
+    if (ends) store(run, 0, bnd);
+    cnt += __popcll(stm);
+    last = readlane64(ex, top64(sm));
+}
+
+// Follow all entries through the block of nb segments at j0 (lane i: segment
+// i's offset and extremes, block coordinates) and leave its runs in X.
+__device__ TmapBlock tmap_block(const Desc& D, int64_t k, int64_t j0, int b, int nb, int32_t T, int32_t Rv, int32_t Sxv,
+                                int32_t Snv, int32_t rend, TmapLds& X) {
+    const int l = lane_id();
+    TmapBuild& B = X.build;
+    SMP_GLOBAL int32_t* sb = tmap_scratch(D, k, b);  // 2 * bound + (below the interval ? 1 : 0)
+    SMP_GLOBAL int32_t* se = sb + TS_SRC;            // exit
+    int nch = 0, nsrc = 0, dead = 0, fail = 0;
+    int32_t Umax = 0, Umin = 0;
+    bool open = true;
+    for (int i = l; i < SEG; i += 64) B.u.s.claim[i] = 0;
+    int32_t pf[NW];  // the next segment's prefixes, loading
+    if (nb > 0) load_kept32(D, j0, pf);
+    for (int s = 0; s < nb && !fail; ++s) {
+        const int32_t R = readlane32(Rv, s), Sx = readlane32(Sxv, s), Sn = readlane32(Snv, s);
+        int nst = 0;
+        for (int c0 = 0; c0 < nch; c0 += 64 * TS_UNROLL) {  // (the groups' reads overlap)
+            int32_t x[TS_UNROLL];
+#pragma unroll
+            for (int q = 0; q < TS_UNROLL; ++q) {
+                const int c = c0 + 64 * q + l;
+                x[q] = c < nch ? B.cx[c] : TS_DEAD;
+            }
+#pragma unroll
+            for (int q = 0; q < TS_UNROLL; ++q) {
+                const bool st = x[q] != TS_DEAD && (x[q] <= Sx - T || x[q] >= Sn + T);
+                const uint64_t m = ballot(st);
+                if (st) B.u.s.lst[nst + __popcll(m & lanemask_lt())] = (uint16_t)(c0 + 64 * q + l);
+                nst += __popcll(m);
+            }
+        }
+        const bool fresh = open && (Sx > Umax || Sn < Umin);
+        int32_t cur[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) cur[w] = pf[w];
+        load_kept32(D, j0 + (s + 1 < nb ? s + 1 : s), pf);
+        if (nst) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) B.u.s.f[w * 64 + l] = cur[w];
+        }
+        if (nst) {
+            // the running extremes of the eight-node groups
+            const v4i32 a = *(const v4i32*)&B.u.s.f[8 * l], c4 = *(const v4i32*)&B.u.s.f[8 * l + 4];
+            int32_t gx = a[0], gn = a[0];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                gx = a[i] > gx ? a[i] : gx;
+                gx = c4[i] > gx ? c4[i] : gx;
+                gn = a[i] < gn ? a[i] : gn;
+                gn = c4[i] < gn ? c4[i] : gn;
+            }
+            gx = wave_incl_ext32<true>(gx);
+            gn = wave_incl_ext32<false>(gn);
+            for (int i0 = 0; i0 < nst; i0 += 64) {
+                const bool mine = i0 + l < nst;
+                const int c = mine ? B.u.s.lst[i0 + l] : 0;
+                const int32_t x = B.cx[c], xr = mine ? x - R : 0;
+                const int root = B.cr[c];
+                int32_t v;
+                const int node = first_samples(B.u.s.f, gx, gn, T, xr, v);
+                // chains that sample at one node merge into the one that claims it
+                // (an LDS exchange in place of these three accesses: 4 % slower)
+                const uint32_t key = (uint32_t)(s + 1) << 16 | (uint32_t)root;
+                uint32_t got = mine ? B.u.s.claim[node] : 0;
+                const bool taken = (got >> 16) == (uint32_t)(s + 1);
+                if (mine && !taken) B.u.s.claim[node] = key;
+                asm volatile("" ::: "memory");  // (several lanes may write one claim: what it holds is read back)
+                if (mine && !taken) got = B.u.s.claim[node];
+                const bool win = mine && got == key;
+                if (mine) B.cx[c] = win ? R + v : TS_DEAD;
+                if (mine && !win) B.par[root] = (uint16_t)(got & 0xFFFFu);
+                dead += __popcll(ballot(mine && !win));
+            }
+        }
+        if (fresh) {
+            // nodes beyond the extremes so far: first samples of unsampled entries
+            int32_t cm = Umax, cn = Umin;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                if (fail || cm - cn > 2 * T - 2) break;
+                const int32_t gv = R + cur[w];
+                if (!ballot(gv > cm || gv < cn)) continue;
+                int32_t im = wave_incl_ext32<true>(gv), in = wave_incl_ext32<false>(gv);
+                im = im > cm ? im : cm;
+                in = in < cn ? in : cn;
+                const int32_t pm = wave_shr1_32(im, cm), pn = wave_shr1_32(in, cn);  // before the node
+                const bool op = pm - pn <= 2 * T - 2;
+                const bool up = op && gv > pm, dn = op && gv < pn;
+                const uint64_t spm = ballot(up || dn);
+                cm = readlane32(im, 63);
+                cn = readlane32(in, 63);
+                const int cnt = __popcll(spm);
+                if (nsrc + cnt > TS_SRC) {
+                    fail = TMF_SOURCES;
+                    break;
+                }
+                const bool mine = (spm >> l) & 1;
+                const int src = nsrc + __popcll(spm & lanemask_lt());
+                const uint32_t cl = mine ? B.u.s.claim[w * 64 + l] : 0;
+                const bool hit = (cl >> 16) == (uint32_t)(s + 1);
+                const uint64_t nm = spm & ~ballot(hit);  // new chains
+                if (nch + __popcll(nm) > TS_CAP) {
+                    fail = TMF_CHAINS;
+                    break;
+                }
+                if (mine) {
+                    sb[src] = up ? 2 * (pn + T - 1 < gv - T ? pn + T - 1 : gv - T) + 1
+                                 : 2 * (pm - T + 1 > gv + T ? pm - T + 1 : gv + T);
+                    B.par[src] = (uint16_t)(hit ? (cl & 0xFFFFu) : (uint32_t)src);
+                }
+                if ((nm >> l) & 1) {
+                    const int o = nch + __popcll(nm & lanemask_lt());
+                    B.cx[o] = gv;
+                    B.cr[o] = (uint16_t)src;
+                }
+                nsrc += cnt;
+                nch += __popcll(nm);
+            }
+        }
+        Umax = Sx > Umax ? Sx : Umax;
+        Umin = Sn < Umin ? Sn : Umin;
+        open = open && Umax - Umin <= 2 * T - 2;
+        if (dead >= 64 || (dead && nch > TS_CAP - 192)) {  // drop the merged chains (survivors never move up)
+            int out = 0;
+            for (int c0 = 0; c0 < nch; c0 += 64) {
+                const int c = c0 + l;
+                const int32_t x = c < nch ? B.cx[c] : TS_DEAD;
+                const uint16_t r = c < nch ? B.cr[c] : 0;
+                const uint64_t m = ballot(x != TS_DEAD);
+                asm volatile("" ::: "memory");
+                if (x != TS_DEAD) {
+                    const int o = out + __popcll(m & lanemask_lt());
+                    B.cx[o] = x;
+                    B.cr[o] = r;
+                }
+                out += __popcll(m);
+            }
+            nch = out;
+            dead = 0;
+        }
+    }
+    TmapBlock r{0, 0, 1, 0, rend, fail};
+    if (fail) return r;
+    if (open) {
+        r.lo = Umax - T + 1;
+        r.hi = Umin + T - 1;
+    }
+    // each source's exit: its root's chain
+    asm volatile("" ::: "memory");
+    for (int c0 = 0; c0 < nch; c0 += 64)
+        if (c0 + l < nch && B.cx[c0 + l] != TS_DEAD) B.u.cidx[B.cr[c0 + l]] = (uint16_t)(c0 + l);
+    asm volatile("" ::: "memory");
+    for (int s0 = 0; s0 < nsrc; s0 += 64) {
+        const int src = s0 + l;
+        if (src < nsrc) {
+            int id = src;
+            for (int d = 0; d < TS_SRC && B.par[id] != id; ++d) id = B.par[id];
+            se[src] = B.cx[B.u.cidx[id]] - rend;
+        }
+    }
+    // the runs of both sides (what this wave stored above is read back, and
+    // the words of the build are done with)
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    int64_t lastU = 0, lastD = 0;
+    for (int s0 = 0; s0 < nsrc; s0 += 64) {
+        const int src = s0 + l;
+        const bool v = src < nsrc;
+        const int32_t b2 = v ? sb[src] : 0, ex = v ? se[src] : 0;
+        add_runs(v && (b2 & 1), ex, b2 >> 1, r.nup, lastU,
+                 [&](int run, int which, int64_t x) { (which ? X.runs.e : X.runs.b)[run] = (int32_t)x; });
+        add_runs(v && !(b2 & 1), ex, b2 >> 1, r.ndn, lastD,
+                 [&](int run, int which, int64_t x) { (which ? X.runs.e : X.runs.b)[TS_SRC - 1 - run] = (int32_t)x; });
+    }
+    return r;
+}
+
+// First of n bounds at p (step d: 1 upward, -1 from the back) that is >= e (GE) or <= e.
+template <bool GE>
+__device__ __forceinline__ int first_bound(const int32_t* p, int d, int n, int32_t e) {
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        const int32_t b = p[d * mid];
+        if (GE ? b >= e : b <= e) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+__device__ __forceinline__ int32_t runs_exit(const TmapRuns& M, const TmapBlock& m, int32_t e) {
+    if (e >= m.lo && e <= m.hi) return e - (int32_t)m.rend;
+    const int u = first_bound<true>(M.b, 1, m.nup, e);
+    if (u < m.nup) return M.e[u];
+    const int d = first_bound<false>(M.b + TS_SRC - 1, -1, m.ndn, e);
+    return M.e[TS_SRC - 1 - (d < m.ndn ? d : 0)];
+}
+
+// One workgroup per tile (grid: every tile of the launch; tiles of traces
+// without maps return at once).  2e7 events at T = 64 MiB (77 tiles): 0.21 ms
+// (a tile: 134 us of block builds, 19 us waiting for the slowest, 8 us of
+// composing; chaining the tiles 0.4 us each), 0.88 ms with one wave per tile.
+// 5e8 events (1,908 tiles, one workgroup per CU at a time): 1.50 ms with the
+// chaining beside the builds, 2.2 ms with it after them, 1.97 ms with one wave
+// per tile.
+__global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, int ntraces, unsigned long long* ctl,
+                                               uint64_t* ts) {
+    stamp(ts);
+    __shared__ union {
+        TmapLds blk[TWAVES];
+        TmapWide wide;
+    } u_;
+    __shared__ TmapRuns pieces;  // the tile's map so far (runs not yet joined)
+    __shared__ TmapBlock s_blk[TWAVES];
+    __shared__ int s_bad[TWAVES];  // 1: the tile does not qualify, 2: it needs the wide path
+    __shared__ int64_t s_ext[3][TWAVES];  // each block's footprint change, largest and smallest footprint
+    __shared__ int s_new[TWAVES];  // segments with a new extreme while entries are unsampled
+    const int tid = threadIdx.x, l = lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint64_t tk = blockIdx.x;
+    const Desc& D = desc[find_trace_tile(desc, ntraces, tk)];
+    if (!D.tmap) return;
+    const int64_t k = (int64_t)(tk - D.tile_begin);
+    const int64_t ns = (int64_t)D.nseg;
+    const int nval = (int)((ns - k * TILE) < TILE ? (ns - k * TILE) : TILE);
+    const int64_t T = D.T;
+    SMP_GLOBAL int64_t* map = tile_map(D, k);
+    const bool valid = tid < nval;
+    const SMP_GLOBAL int64_t* sp = gp(D.seg) + k * TILE + (valid ? tid : 0);
+    // every segment SIM, with a no-sample interval of at least T entries
+    // (then max - min < T over its prefixes and the entry)
+    int64_t af = 0, mx = 0, mn = 0;
+    int32_t Rv, Sxv, Snv;
+    {
+        const int64_t lo = sp[SP_LO * ns], hi = sp[SP_HI * ns], fl = sp[SP_FLG * ns];
+        if (valid) {
+            af = sp[SP_AF * ns];
+            mx = sp[SP_MXF * ns];
+            mn = sp[SP_MNF * ns];
+        }
+        const bool no = valid && ((fl & 3) != MAP_SIM || hi < lo || hi - lo < T - 1);
+        const int64_t R = wave_incl_sum(af) - af;
+        const bool in = R + mx < KEPT32 && R + mn > -KEPT32 && (fl & FLG_FIT);
+        const int bad = ballot(no) || !prefixes_kept(D) ? 1 : (ballot(valid && !in) || T >= KEPT32 ? 2 : 0);
+        const int64_t im = wave_incl_max(R + mx), in_ = wave_incl_min(R + mn);
+        if (l == 63) {
+            s_bad[wv] = bad;
+            s_ext[0][wv] = R + af;
+            s_ext[1][wv] = im;
+            s_ext[2][wv] = in_;
+        }
+        Rv = (int32_t)R;
+        Sxv = (int32_t)(R + mx);
+        Snv = (int32_t)(R + mn);
+        __syncthreads();
+        // the tile's extremes before this block, then before each segment
+        int64_t base = 0, x = 0, n = 0;
+        for (int w = 0; w < wv; ++w) {
+            x = base + s_ext[1][w] > x ? base + s_ext[1][w] : x;
+            n = base + s_ext[2][w] < n ? base + s_ext[2][w] : n;
+            base += s_ext[0][w];
+        }
+        const int64_t pm = wave_shr1(im, INT64_MIN), pn = wave_shr1(in_, INT64_MAX);
+        const int64_t bx = l && base + pm > x ? base + pm : x, bn = l && base + pn < n ? base + pn : n;
+        const int c = __popcll(
+            ballot(valid && bx - bn <= 2 * T - 2 && (base + R + mx > bx || base + R + mn < bn)));
+        if (l == 0) s_new[wv] = c;
+    }
+    __syncthreads();
+    int bad = 0, fresh_segs = 0;
+    for (int w = 0; w < TWAVES; ++w) {
+        bad = bad == 1 || s_bad[w] == 1 ? 1 : (bad | s_bad[w]);
+        fresh_segs += s_new[w];
+    }
+    int fail = bad == 1 ? TMF_QUALIFY : 0;
+    // A tile whose entries take too long to sample would start more chains
+    // than a map holds (~31 sources per segment with a new extreme on the
+    // log-uniform mixes, and then too many runs): found out here, not after
+    // a build of 0.2 to 0.4 ms.
+    if (!fail && fresh_segs > TS_FRESH) {
+        bad = 1;
+        fail = TMF_SOURCES;
+    }
+    if (bad == 2) {
+        if (wv) return;
+        fail = tmap_wide(D, k, nval, u_.wide, map);
+    } else if (bad == 0) {
+        const int nb = nval - wv * 64 < 0 ? 0 : (nval - wv * 64 < 64 ? nval - wv * 64 : 64);
+        const int32_t rend = readlane32(Rv + (int32_t)af, 63);
+        const TmapBlock mine = tmap_block(D, k, k * TILE + wv * 64, wv, nb, (int32_t)T, Rv, Sxv, Snv, rend, u_.blk[wv]);
+        if (l == 0) s_blk[wv] = mine;
+        __syncthreads();
+        for (int w = 0; w < TWAVES; ++w) fail = fail ? fail : s_blk[w].fail;
+        // Compose: every piece's exit through the next block's map, and what
+        // is left unsampled cut by that block's runs.
+        int nup = 0, ndn = 0;
+        int64_t Ulo = -T + 1, Uhi = T - 1, tF = 0;
+        for (int w = 0; w < TWAVES && !fail; ++w) {
+            const TmapBlock m = s_blk[w];
+            const TmapRuns& M = u_.blk[w].runs;
+            for (int i = tid; i < nup + ndn; i += TILE) {
+                const int at = i < nup ? i : TS_SRC - 1 - (i - nup);
+                pieces.e[at] = runs_exit(M, m, pieces.e[at]);
+            }
+            if (Ulo <= Uhi) {
+                // (an unsampled entry stays inside (-T, T) of every segment's start)
+                const int32_t a = (int32_t)(Ulo - tF), z = (int32_t)(Uhi - tF);
+                const int u0 = first_bound<true>(M.b, 1, m.nup, a), u1 = first_bound<true>(M.b, 1, m.nup, z);
+                const int nu = u0 < m.nup ? (u1 < m.nup ? u1 : m.nup - 1) - u0 + 1 : 0;
+                const int32_t* db = M.b + TS_SRC - 1;
+                const int d0 = first_bound<false>(db, -1, m.ndn, z), d1 = first_bound<false>(db, -1, m.ndn, a);
+                const int nd = d0 < m.ndn ? (d1 < m.ndn ? d1 : m.ndn - 1) - d0 + 1 : 0;
+                if (nup + ndn + nu + nd > TS_SRC) {
+                    fail = TMF_SOURCES;
+                    break;
+                }
+                for (int i = tid; i < nu; i += TILE) {
+                    const int32_t b = M.b[u0 + i];
+                    pieces.b[nup + i] = (int32_t)((b < z ? b : z) + tF);
+                    pieces.e[nup + i] = M.e[u0 + i];
+                }
+                for (int i = tid; i < nd; i += TILE) {
+                    const int32_t b = db[-(d0 + i)];
+                    pieces.b[TS_SRC - 1 - (ndn + i)] = (int32_t)((b > a ? b : a) + tF);
+                    pieces.e[TS_SRC - 1 - (ndn + i)] = M.e[TS_SRC - 1 - (d0 + i)];
+                }
+                nup += nu;
+                ndn += nd;
+                if (m.lo > m.hi) {
+                    Uhi = Ulo - 1;
+                } else {
+                    Ulo = m.lo + tF > Ulo ? m.lo + tF : Ulo;
+                    Uhi = m.hi + tF < Uhi ? m.hi + tF : Uhi;
+                }
+            }
+            tF += m.rend;
+            __syncthreads();
+        }
+        if (wv) return;
+        // the tile's runs, stored through to memory (another wave reads them in this launch)
+        int ru = 0, rd = 0;
+        int64_t lastU = 0, lastD = 0;
+        for (int g = 0; g < nup && !fail && ru <= TM_SIDE; g += 64) {
+            const bool v = g + l < nup;
+            add_runs(v, v ? pieces.e[g + l] : 0, v ? pieces.b[g + l] : 0, ru, lastU, [&](int run, int which, int64_t x) {
+                if (run < TM_SIDE) st_map(map + run_word(0, which, run), x);
+            });
+        }
+        for (int g = 0; g < ndn && !fail && rd <= TM_SIDE; g += 64) {
+            const bool v = g + l < ndn;
+            const int at = TS_SRC - 1 - (v ? g + l : 0);
+            add_runs(v, v ? pieces.e[at] : 0, v ? pieces.b[at] : 0, rd, lastD, [&](int run, int which, int64_t x) {
+                if (run < TM_SIDE) st_map(map + run_word(1, which, run), x);
+            });
+        }
+        if (ru > TM_SIDE || rd > TM_SIDE) fail = fail ? fail : TMF_RUNS;
+        if (!fail && l == 0) {
+            st_map(map + TM_HDR + 1, ru);
+            st_map(map + TM_HDR + 2, rd);
+            st_map(map + TM_HDR + 3, tF);
+        }
+    }
+    if (wv) return;
     if (l == 0) {
         st_map(map + TM_HDR, fail ? TM_NONE : TM_MAPPED);
         g_add((uint64_t*)&ctl[fail ? 6 + fail : 5], 1ull);
     }
-    // The last of the trace's tile waves chains its tiles.  The map's words
-    // were stored through to memory (agent-scope stores): it is counted once
-    // they are complete, and the last wave drops any stale copies of other
-    // tiles' words from its caches before it reads them.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    uint64_t done = 0;
-    if (l == 0) done = g_add_rtn(&D.scal->tmap_done, 1ull);
-    if (readlaneu64(done, 0) == D.ntile - 1) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        chain_maps(D, ctl);
-    }
+    chain_done_tiles(D, k, ctl);
 }
 
 // ------------------------------------------------------------ block maps
@@ -1735,28 +2205,10 @@ __device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int n
     // one node merged, the rest of the segment one chain after another.
     auto stop_group = [&](uint64_t& al, uint64_t st, int32_t& X, int id, int32_t R, int s, bool single, int32_t cgx,
                           int32_t cgn) {
-        const uint32_t span = (uint32_t)(2 * T - 1);
         const bool mine = (st >> l) & 1;
         const int32_t xr = mine ? X - R : 0;
-        const int32_t hi = xr + T, lo = xr - T;
-        int g = 0;
-#pragma unroll
-        for (int d = 32; d; d >>= 1) {
-            const int32_t x = shfl32(cgx, g + d - 1), n = shfl32(cgn, g + d - 1);
-            g += x >= hi || n <= lo ? 0 : d;
-        }
-        g &= 63;  // (a stopping chain crosses in some group)
-        const v4i32 a = *(const v4i32*)&B.f[8 * g], b = *(const v4i32*)&B.f[8 * g + 4];
-        int e = 7;
-        int32_t v = b[3];
-#pragma unroll
-        for (int i = 6; i >= 0; --i) {
-            const int32_t y = i < 4 ? a[i & 3] : b[i & 3];
-            const bool c = (uint32_t)(y + (T - 1) - xr) >= span;
-            e = c ? i : e;
-            v = c ? y : v;
-        }
-        const int node = 8 * g + e;
+        int32_t v;
+        const int node = first_samples(B.f, cgx, cgn, T, xr, v);
         const uint32_t tag = (uint32_t)(s + 1) << 9, key = tag | (uint32_t)id;
         uint32_t got = mine ? B.claim[node] : 0;
         const bool taken = (got >> 9) == (uint32_t)(s + 1);
@@ -3604,7 +4056,7 @@ hipError_t launch_clear(const Desc* desc, int ntraces, uint64_t total_bytes, uns
 hipError_t launch_tmap(const Desc* desc, int ntraces, uint64_t ntile_total, unsigned long long* ctl, uint64_t* ts,
                        hipStream_t s) {
     if (ntile_total == 0) return hipSuccess;
-    k_tmap<<<dim3((unsigned)ntile_total), dim3(64), 0, s>>>(desc, ntraces, ctl, ts);
+    k_tmap<<<dim3((unsigned)ntile_total), dim3(TILE), 0, s>>>(desc, ntraces, ctl, ts);
     return hipGetLastError();
 }
 
