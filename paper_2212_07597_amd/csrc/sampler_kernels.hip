@@ -419,6 +419,42 @@ __device__ SegMap analyse_segment(const int64_t* F, int64_t T, int64_t sumF, int
     return m;
 }
 
+// The same for a segment that moves less than T, from its extremes: an entry
+// samples at most once in it, at the first node beyond all earlier ones that
+// is T away, and every node beyond all earlier ones is that for some entry.
+// So the segment has one chain (a constant exit) only if there is one such
+// node: if the first node away from 0 is an extreme already and the other
+// side has none.  Summary pass, against following the chains: 2e7 events at
+// T = 64 MiB 150 -> 118 us, 1,024 traces at T up to 10 MiB 1.07 -> 0.98 ms
+// (5e8 events, bound by memory: unchanged at 3.26 ms).
+__device__ __forceinline__ bool still_segment(const int64_t* F, int64_t T, int64_t sumF, int64_t mx, int64_t mn,
+                                              SegMap& m) {
+    const int64_t hi = sgt64(mx, 0) ? mx : 0, lo = sgt64(0, mn) ? mn : 0;
+    if (!sgt64(T, hi - lo)) return false;
+    m.fnode = -1;
+    m.lo = hi - T + 1;
+    m.hi = lo + T - 1;
+    m.kf = 0;
+    m.kind = MAP_SIM;
+    if ((hi == 0) != (lo == 0)) {
+        const int64_t x = hi - lo == hi ? hi : lo;  // the one extreme
+        int64_t first = 0;
+        for (int w = 0; w < NW; ++w) {
+            const int64_t f = F[w * 64 + lane_id()];
+            const uint64_t a = ballot(f != 0);
+            if (a) {
+                first = readlane64(f, ctz64(a));
+                break;
+            }
+        }
+        if (first == x) {
+            m.kind = MAP_CONST;
+            m.kf = x - sumF;
+        }
+    }
+    return true;
+}
+
 // ---------------------------------------------------------------- look-backs
 
 // Every wait on another tile's status polls with a budget and an exponential
@@ -786,7 +822,7 @@ __device__ __forceinline__ void summarize_segment(const Desc& D, uint64_t g, int
         p += cP;
         cF = readlane64(f, 63);
         cP = readlane64(p, 63);
-        lF_[k] = f;
+        if (fnode < 0) lF_[k] = f;  // (only the all-entry analysis reads them)
         if (fnode < 0 && fm) {
             // The first forced event: entries in [plo, phi] take no sample
             // before it (the prefix's extremes: earlier windows, then the
@@ -842,7 +878,7 @@ __device__ __forceinline__ void summarize_segment(const Desc& D, uint64_t g, int
         m.kind = MAP_TOTAL;
         m.fnode = fnode;
     } else {
-        m = analyse_segment(lF_, T, cF, (int)D.chain_cap);
+        if (!still_segment(lF_, T, cF, sc.mxF, sc.mnF, m)) m = analyse_segment(lF_, T, cF, (int)D.chain_cap);
         if (m.kind == MAP_SIM && prefixes_kept(D)) {
             if (sgt64(KEPT32, sc.mxF) && sgt64(sc.mnF, -KEPT32)) {
                 fit = FLG_FIT;

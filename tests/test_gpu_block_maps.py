@@ -67,3 +67,26 @@ def test_mixed_segments(sampler):
              ("quiet small T", quiet, 2 * tg.MiB), ("wide", wide, (1 << 29) + 1), ("wide below", wide, (1 << 30) - 1),
              ("wide at", wide, 1 << 30), ("edge", edge, 10 * tg.MiB), ("edge high", edge, (1 << 30) - 1)]
     check(sampler, [(label, ev, dict(threshold=T, num_lines=9)) for label, ev, T in cases])
+
+
+def test_still_segments(sampler):
+    """Segments that move less than T, whose map comes from their extremes:
+    one extreme reached at once (constant exit), reached by steps, on both
+    sides, from the other side first, and no movement at all."""
+    def trace(*segments):
+        d = np.zeros(len(segments) * SEG, np.int64)
+        for i, steps in enumerate(segments):
+            for at, x in steps:
+                d[i * SEG + at] = x
+        ev = np.zeros(d.shape[0], dtype=tg.EVENT_DTYPE)
+        ev["delta"] = d
+        ev["ptr"] = np.arange(1, d.shape[0] + 1)
+        ev["line"] = np.arange(d.shape[0]) % 5
+        return ev
+    shapes = [[(0, 40)], [(511, 40)], [(3, 40), (70, -10)], [(3, 40), (70, -45)], [(3, -30)], [(3, -30), (90, 55)],
+              [(9, 20), (400, 20)], [(9, 20), (80, -20), (300, 20)], [(5, 1)], [(5, -1)], [], [(64, 99)], [(63, -99)],
+              [(0, 50), (1, -100)], [(0, 49), (1, -99), (2, 99)]]
+    rng = np.random.default_rng(4)
+    order = [shapes[i] for i in rng.integers(0, len(shapes), 300)]
+    cases = [(f"still T{T}", trace(*order), dict(threshold=T, num_lines=5)) for T in (50, 100, 101, 150, 1000)]
+    check(sampler, cases)
