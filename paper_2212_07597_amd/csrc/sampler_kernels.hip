@@ -930,15 +930,28 @@ __device__ __forceinline__ void summarize_segment(const Desc& D, uint64_t g, int
     if (sc.err && l == 0) g_or32(&D.scal->err, sc.err);
 }
 
+// The work of workgroup b when each XCD takes runs of XCD_RUN consecutive
+// workgroups' work (workgroups are dealt to the 8 XCDs in turn; the last,
+// incomplete round stays in order).
+constexpr uint64_t XCDS = 8, XCD_RUN = 16;
+__device__ __forceinline__ uint64_t xcd_block(uint64_t b, uint64_t n) {
+    const uint64_t first = b / (XCDS * XCD_RUN) * (XCDS * XCD_RUN), r = b - first;
+    return first + XCDS * XCD_RUN <= n ? first + r % XCDS * XCD_RUN + r / XCDS : b;
+}
+
 // One wave per segment, one launch wave per segment (measured faster here
 // than a grid-stride loop: the hardware starts a new wave's loads while
-// others compute).
+// others compute).  Runs of 16 workgroups per XCD: a segment writes 8 bytes to
+// each of 23 planes, and the 128-byte lines of 16 segments then fill up in one
+// XCD's L2 instead of going out in pieces from eight.  1e8 events 518 -> 460 us
+// (5.2 TB/s of records), 5e8 events 3.0 -> 2.76 ms; runs of 2 and 4: 510 and
+// 499 us, of 8 to 64: 448 to 470.
 __global__ __launch_bounds__(BLOCK) void k_summarize(const Desc* __restrict__ desc, int ntraces,
                                                      uint64_t nseg_total, uint64_t* ts) {
     __shared__ int64_t lF[WAVES][SEG];
     stamp(ts);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-    const uint64_t g = (uint64_t)blockIdx.x * WAVES + wv;
+    const uint64_t g = xcd_block(blockIdx.x, gridDim.x) * WAVES + wv;
     if (g >= nseg_total) return;
     summarize_segment(desc[__builtin_amdgcn_readfirstlane(find_trace_seg(desc, 0, ntraces, g))], g, lF[wv]);
 }
