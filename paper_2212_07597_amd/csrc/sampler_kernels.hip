@@ -2087,11 +2087,12 @@ __global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, in
 // would start more chains than fit); a tile that does not qualify, or whose
 // blocks start more, is walked instead.
 // Bound: the serial chain of one wave through 64 segments (a sample of a lone
-// chain costs ~250 ns of dependent ballots and LDS reads; the first samples of
+// chain costs ~150 ns of dependent ballots and LDS reads; the first samples of
 // many chains are searched side by side).  Measured, resolve pass: 1,024
-// traces of 1e3-1e6 events at T = 256 KiB / 1 MiB / 10 MiB 1.12 -> 0.32 ms; a
-// trace of 777,777 events at T = 3 MiB (three tiles) 1.53 -> 0.17 ms; one of
-// 1.2e7 events at T = 10 MiB 9.5 -> 0.2 ms.  A tile of few SIM segments
+// traces of 1e3-1e6 events at T = 256 KiB / 1 MiB / 10 MiB 1.12 -> 0.28 ms; a
+// trace of 777,777 events at T = 3 MiB (three tiles) 1.53 -> 0.15 ms; one of
+// 1.2e7 events at T = 10 MiB 9.5 -> 0.2 ms.  (Prefixes two segments ahead
+// instead of one: 25 spilled registers and 0.16 / 0.29 ms.)  A tile of few SIM segments
 // (below BM_MIN_SIM) walks them in less time than a block map takes.
 constexpr int BM_SRC = 512;   // sources per block
 constexpr int BM_OPEN = 14;   // ~31 sources per segment on the log-uniform mixes while entries are left
@@ -2136,38 +2137,49 @@ struct BlockMap {
     int32_t ref;
 };
 
-// The next sample of a chain in a segment whose prefixes lie in f and whose
-// eight-node groups (lane g: nodes 8g .. 8g + 7) reach from gn to gx: one
-// ballot over the groups, one over the nodes of the first group that crosses.
-// The search goes on from node 8 * gfrom + efrom; a crossing group whose
-// crossings all lie before it is passed over.
-struct NextSample {
-    int node;     // SEG: none
-    int32_t f;
-    uint32_t claim;
-};
-__device__ __forceinline__ NextSample next_sample(const BlockLds& B, int32_t gx, int32_t gn, int32_t T, int32_t xr,
-                                                  int from) {
+// Follow a chain from reference xr (relative to the segment) from node st on
+// through a segment whose prefixes lie in B.f and whose eight-node groups
+// (lane g: nodes 8g .. 8g + 7) reach from gn to gx: each sample takes two
+// ballots over the groups and one over the nodes of the first group that
+// crosses.  CLAIM: every sampled node is claimed (tag: the segment's bits of
+// a claim, id: the chain); returns the chain that had claimed one, or -1 at
+// the segment end.  one: stop after a sample (a segment that moves less than
+// T holds one of a chain).
+template <bool CLAIM>
+__device__ __forceinline__ int follow_groups(BlockLds& B, int32_t gx, int32_t gn, int32_t T, int32_t& xr, int st,
+                                             uint32_t tag, uint32_t id, bool one) {
     const int l = lane_id();
     const uint32_t span = (uint32_t)(2 * T - 1);
-    NextSample r{SEG, 0, 0};
-    uint64_t gm = from < SEG ? ballot(gx >= xr + T || gn <= xr - T) & (~0ull << (from >> 3)) : 0;
-    while (gm) {
-        const int g = ctz64(gm);
-        const int32_t v = B.f[8 * g + (l & 7)];
-        const uint32_t c = B.claim[8 * g + (l & 7)];
-        uint64_t m = ballot((uint32_t)(v + (T - 1) - xr) >= span) & 0xFFull;
-        if (8 * g < from) m &= ~0ull << (from & 7);
-        if (m) {
-            const int j = ctz64(m);
-            r.node = 8 * g + j;
-            r.f = readlane32(v, j);
-            r.claim = (uint32_t)readlane32((int)c, j);
-            break;
+    if (st >= SEG) return -1;
+    int gfrom = st >> 3;
+    uint64_t emask = (0xFFull << (st & 7)) & 0xFFull, gmask = ~0ull << gfrom;
+    for (;;) {
+        uint64_t gm = (ballot(gx >= xr + T) | ballot(gn <= xr - T)) & gmask, m;
+        int g;
+        int32_t v;
+        uint32_t c = 0;
+        for (;;) {
+            if (!gm) return -1;
+            g = ctz64(gm);
+            v = B.f[8 * g + (l & 7)];
+            if (CLAIM) c = B.claim[8 * g + (l & 7)];
+            asm volatile("" : "+v"(v), "+v"(c));  // (both reads in flight together)
+            m = ballot((uint32_t)(v + (T - 1) - xr) >= span) & (g == gfrom ? emask : 0xFFull);
+            if (m) break;
+            gm &= gm - 1;  // (the first group's crossings lie before st)
         }
-        gm &= gm - 1;
+        const int j = ctz64(m);
+        if (CLAIM) {
+            const uint32_t cj = (uint32_t)readlane32((int)c, j);
+            if ((cj & ~BM_ID) == tag) return (int)(cj & BM_ID);
+            B.claim[8 * g + j] = (uint16_t)(tag | id);
+        }
+        xr = readlane32(v, j);
+        if (one) return -1;
+        gfrom = g;
+        gmask = ~0ull << g;
+        emask = (0xFEull << j) & 0xFFull;
     }
-    return r;
 }
 
 // Build the map of the block at segment j0 of nb segments; lane i holds
@@ -2192,10 +2204,7 @@ __device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int n
     };
     // segment s's prefixes (just prefetched) into LDS, and their group extremes
     int32_t gx = 0, gn = 0;
-    auto take = [&](int s) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) B.f[w * 64 + l] = pf[w];
-        prefetch(s + 1);
+    auto group_extremes = [&]() {
         const v4i32 a = *(const v4i32*)&B.f[8 * l], b = *(const v4i32*)&B.f[8 * l + 4];
         gx = a[0];
         gn = a[0];
@@ -2207,19 +2216,16 @@ __device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int n
             gn = b[i] < gn ? b[i] : gn;
         }
     };
+    auto take = [&](int s) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) B.f[w * 64 + l] = pf[w];
+        prefetch(s + 1);
+        group_extremes();
+    };
     // Follow chain id from reference xr (relative to segment s) from node st
-    // on; the chain it meets, or -1 at the segment end.  (A segment that
-    // moves less than T holds one sample of a chain.)
+    // on; the chain it meets, or -1 at the segment end.
     auto follow = [&](int32_t& xr, int st, int id, int s, bool single) -> int {
-        for (;;) {
-            const NextSample n = next_sample(B, gx, gn, T, xr, st);
-            if (n.node >= SEG) return -1;
-            if ((n.claim >> 9) == (uint32_t)(s + 1)) return (int)(n.claim & BM_ID);
-            B.claim[n.node] = (uint16_t)((s + 1) << 9 | id);
-            xr = n.f;
-            st = n.node + 1;
-            if (single) return -1;
-        }
+        return follow_groups<true>(B, gx, gn, T, xr, st, (uint32_t)(s + 1) << 9, (uint32_t)id, single);
     };
     // Columns for the new chains of the lanes in nm (reference X, name id).
     auto new_columns = [&](uint64_t nm, int32_t X, int id) {
@@ -2404,33 +2410,31 @@ __device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int n
                         B.cseg[src] = (uint8_t)s;
                         B.par[src] = (uint16_t)src;
                     }
-                    if (single) {  // (no chain samples again: all at once)
-                        const uint32_t cl = mine ? B.claim[w * 64 + l] : 0;
-                        const bool hit = (cl >> 9) == (uint32_t)(s + 1);
-                        if (mine) {
-                            B.init[src] = (uint16_t)(hit ? (int)(cl & BM_ID) : src);
-                            if (!hit) B.claim[w * 64 + l] = (uint16_t)((s + 1) << 9 | src);
-                        }
-                        new_columns(spm & ~ballot(hit), gv, src);
-                        nsrc += __popcll(spm);
-                        continue;
+                    const uint32_t cl = mine ? B.claim[w * 64 + l] : 0;
+                    const bool hit = (cl >> 9) == (uint32_t)(s + 1);
+                    if (mine) {
+                        B.init[src] = (uint16_t)(hit ? (int)(cl & BM_ID) : src);
+                        if (!hit) B.claim[w * 64 + l] = (uint16_t)((s + 1) << 9 | src);
                     }
-                    for (uint64_t m = spm; m && ok; m &= m - 1) {
-                        const int c = ctz64(m), sc = nsrc++;
-                        const uint32_t cl = (uint32_t)__builtin_amdgcn_readfirstlane((int)B.claim[w * 64 + c]);
-                        if ((cl >> 9) == (uint32_t)(s + 1)) {
-                            B.init[sc] = (uint16_t)(cl & BM_ID);
-                            continue;
-                        }
-                        B.claim[w * 64 + c] = (uint16_t)((s + 1) << 9 | sc);
-                        B.init[sc] = (uint16_t)sc;
+                    const uint64_t nm = spm & ~ballot(hit);
+                    new_columns(nm, gv, src);
+                    nsrc += __popcll(spm);
+                    if (single) continue;  // (no chain samples again)
+                    for (uint64_t m = nm; m && ok; m &= m - 1) {
+                        const int c = ctz64(m), id = readlane32(src, c);
                         int32_t xr = readlane32(fv, c);
-                        const int to = follow(xr, w * 64 + c + 1, sc, s, false);
+                        const int32_t x0 = xr;
+                        const int to = follow(xr, w * 64 + c + 1, id, s, false);
+                        if (to < 0 && xr == x0) continue;
+                        const int col = readlane32((int)B.slot[id], 0);
                         if (to >= 0) {
-                            B.par[sc] = (uint16_t)to;
-                            B.mseg[sc] = (uint8_t)s;
+                            B.par[id] = (uint16_t)to;
+                            B.mseg[id] = (uint8_t)s;
+                            alA &= col < 64 ? ~(1ull << col) : ~0ull;
+                            alB &= col < 64 ? ~0ull : ~(1ull << (col - 64));
                         } else {
-                            new_columns(1ull, R + xr, sc);
+                            XA = l == col ? R + xr : XA;
+                            XB = 64 + l == col ? R + xr : XB;
                         }
                     }
                 }
@@ -2461,6 +2465,11 @@ __device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int n
         const uint64_t runm =
             ballot(l > 0 && l < nb && kindv != MAP_SIM && (kindv == MAP_TOTAL || kp <= Sxv - T || kp >= Snv + T));
         r.ref = X;
+        auto next_sim = [&](int from) {
+            const uint64_t m = from < 64 ? simm & (~0ull << from) : 0;
+            return m ? ctz64(m) : 64;
+        };
+        int ia = next_sim(s);  // the segment whose prefixes are in pf
         while (s < nb) {
             const uint64_t stop =
                 ballot(l >= s && l < nb && (kindv == MAP_TOTAL || X <= Sxv - T || X >= Snv + T));
@@ -2468,19 +2477,13 @@ __device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int n
             if (!stop) break;
             const int i = ctz64(stop);
             if ((simm >> i) & 1) {
-                // (the prefetch may hold another segment)
-                const uint64_t m = s < 64 ? simm & (~0ull << s) : 0;
-                if (!m || ctz64(m) != i) prefetch(i);
+                if (i != ia) prefetch(i);
                 take(i);
+                ia = next_sim(i + 1);
                 const int32_t R = readlane32(Rv, i);
                 const bool single = readlane32(Sxv, i) - readlane32(Snv, i) < T;
                 int32_t xr = X - R;
-                for (int st = 0; st < SEG;) {
-                    const NextSample n = next_sample(B, gx, gn, T, xr, st);
-                    if (n.node >= SEG) break;
-                    xr = n.f;
-                    st = single ? SEG : n.node + 1;
-                }
+                (void)follow_groups<false>(B, gx, gn, T, xr, 0, 0, 0, single);
                 X = R + xr;
                 if (l >= i) r.ref = X;
                 s = i + 1;
@@ -2490,8 +2493,6 @@ __device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int n
                 const int e = nr ? ctz64(nr) : 64;  // first segment past the run
                 if (l >= i && l < e) r.ref = kxv;
                 X = readlane32(kxv, e - 1);
-                const uint64_t pm = s < 64 ? simm & (~0ull << s) : 0, qm = e < 64 ? simm & (~0ull << e) : 0;
-                if (qm && ctz64(qm) != (pm ? ctz64(pm) : 64)) prefetch(e);
                 s = e;
             }
         }
