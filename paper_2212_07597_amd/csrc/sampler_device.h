@@ -17,10 +17,14 @@ constexpr int WAVES = 4;                 // wavefronts per workgroup of the per-
 constexpr int BLOCK = 64 * WAVES;
 constexpr int TILE = 512;                // segments per tile
 constexpr int TWAVES = TILE / 64;
-constexpr int EMIT_SLOTS = 128;          // emit pass (samples)
-constexpr int TRACK_SLOTS = 64;          // and tracked-list pass (mallocs, frees)
-constexpr int NCNT = 12;                 // counters cached per slot
+constexpr int TRACK_SLOTS = 64;          // line cache of the tracked-list pass (mallocs, frees)
 constexpr int CHAIN_CAP_MAX = 64;        // chains the all-entry analysis can follow (one per lane)
+// Whether the emit pass takes its wide shape (large line tables shared by
+// eight waves): for one trace of 4,096 segments or more, one for each wave that
+// the GPU then holds.  With copies and timers on 100 and on 10,000 lines, wide
+// and narrow: 1 M events 42 and 45, 22 and 21 us; 2 M 73 and 81, 30 and 33;
+// 10 M 145 and 179, 106 and 128.
+inline bool emit_wide(int ntraces, uint64_t nseg) { return ntraces == 1 && nseg >= 4096; }
 constexpr uint64_t TILE_MAP_BYTES = 32768;  // map area per tile (in the tracked-list area)
 constexpr uint64_t TILE_MAP_ROOM = 163840;  // with the scratch of a tile's blocks
 
@@ -29,7 +33,6 @@ constexpr int64_t MAX_ABS_F = (int64_t)1 << 61;
 
 // per-line histogram indices (same order as the public SMP_H_* enum)
 enum { H_PY = 0, H_NAT, H_GN, H_SN, H_GB, H_SB, H_LEAK_M, H_LEAK_F, H_CS, H_CE, H_PT, H_NT, H_COUNT };
-enum { C_PY = 0, C_NAT, C_GN, C_SN, C_GB, C_SB, C_CS, C_CE, C_PT, C_NT, C_LM, C_LF };
 
 // Chain map of a segment over entry offsets: entries in [lo, hi] take no
 // sample; every other entry ends at one exit offset (CONST; TOTAL when the

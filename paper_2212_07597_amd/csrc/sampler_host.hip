@@ -14,7 +14,7 @@
 
 namespace smp {
 int chain_grid_limit();
-int emit_grid_limit();
+int emit_grid_limit(bool wide);
 int track_grid_limit();
 hipError_t launch_clear(const Desc* desc, int ntraces, uint64_t total_bytes, unsigned long long* ctl, hipStream_t s);
 hipError_t launch_pass(int pass, const Desc* desc, int ntraces, uint64_t nseg_total, uint64_t ntile_total,
@@ -230,7 +230,7 @@ struct smp_sampler {
     int next_stream = 0;
     uint64_t next_id = 1;
     uint64_t run_seq = 0;
-    int grid_chain = 0, grid_emit = 0, grid_track = 0;
+    int grid_chain = 0, grid_emit = 0, grid_emit_wide = 0, grid_track = 0;
     double clock_khz = 0;           // rate of the device clock
     hipStream_t fetch_stream = nullptr;
     // Pinned host memory, one block for all slots each: their descriptor
@@ -429,9 +429,10 @@ int sampler_create(int device, void* hip_stream, uint64_t mem_budget, void* work
         }
     }
     s->grid_chain = chain_grid_limit();
-    s->grid_emit = emit_grid_limit();
+    s->grid_emit = emit_grid_limit(false);
+    s->grid_emit_wide = emit_grid_limit(true);
     s->grid_track = track_grid_limit();
-    if (s->grid_chain <= 0 || s->grid_emit <= 0 || s->grid_track <= 0) {
+    if (s->grid_chain <= 0 || s->grid_emit <= 0 || s->grid_emit_wide <= 0 || s->grid_track <= 0) {
         sampler_destroy(s);
         return SMP_EDEVICE;
     }
@@ -595,6 +596,8 @@ int run(smp_sampler_t* s, int blocking) {
         key.ev_mask = s->pass_events;
         key.chain_grid = s->tuning.chain_grid ? s->tuning.chain_grid : (uint64_t)s->grid_chain;
         key.emit_grid = s->tuning.emit_grid ? s->tuning.emit_grid : (uint64_t)s->grid_emit;
+        // (the wide shape's workgroups are larger: no more of them than the GPU holds)
+        if (emit_wide((int)cnt, key.seg)) key.emit_grid = std::min(key.emit_grid, (uint64_t)s->grid_emit_wide);
         key.track_grid = (uint64_t)s->grid_track;
         // A free slot that launched this shape before (its graph or its
         // descriptors may be reused), else the free slot used longest ago,

@@ -34,77 +34,150 @@
 
 namespace smp {
 
-__device__ __forceinline__ int cache_to_hist(int c) {
-    switch (c) {
-        case C_PY: return H_PY;
-        case C_NAT: return H_NAT;
-        case C_GN: return H_GN;
-        case C_SN: return H_SN;
-        case C_GB: return H_GB;
-        case C_SB: return H_SB;
-        case C_CS: return H_CS;
-        case C_CE: return H_CE;
-        case C_PT: return H_PT;
-        case C_NT: return H_NT;
-        case C_LM: return H_LEAK_M;
-        default: return H_LEAK_F;
-    }
-}
-
-// Per-workgroup LDS cache of per-line counters, NS slots (a power of two <= 256).
-template <int NS>
-struct HistCache {
-    unsigned long long key[NS];  // (trace << 32) | line, or ~0 when empty
-    unsigned long long cnt[NS][NCNT];
-};
-
 constexpr unsigned long long EMPTY_KEY = ~0ull;
 
-template <int NS>
-__device__ __forceinline__ void hist_init(HistCache<NS>& hc) {
-    for (int i = threadIdx.x; i < NS; i += blockDim.x) {
-        hc.key[i] = EMPTY_KEY;
-        for (int c = 0; c < NCNT; ++c) hc.cnt[i][c] = 0;
-    }
-}
-
-// Add up to four counters of (trace t, line) through the workgroup's LDS
-// cache; a slot held by another line sends the update to global atomics.
-template <int NS>
-__device__ __forceinline__ void hist_add(HistCache<NS>& hc, const Desc& D, uint32_t t, uint32_t line, int c0,
-                                         int64_t v0, int c1, int64_t v1, int c2, int64_t v2, int c3, int64_t v3) {
-    const unsigned long long key = ((unsigned long long)t << 32) | line;
-    const uint32_t h = (line * 2654435761u) ^ (t * 0x9E3779B9u);
-    const int slot = (int)(h >> 24) & (NS - 1);
-    unsigned long long k = hc.key[slot];
-    if (k == EMPTY_KEY) k = atomicCAS(&hc.key[slot], EMPTY_KEY, key);
-    const int cs[4] = {c0, c1, c2, c3};
-    const int64_t vs[4] = {v0, v1, v2, v3};
-    if (k == EMPTY_KEY || k == key) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (cs[i] >= 0 && vs[i] != 0) atomicAdd(&hc.cnt[slot][cs[i]], (unsigned long long)vs[i]);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (cs[i] >= 0 && vs[i] != 0)
-                g_add((uint64_t*)&D.hist[(size_t)cache_to_hist(cs[i]) * D.L + line], (uint64_t)vs[i]);
-    }
-}
-
-// Move the cache to the per-line histograms (whole workgroup, after a barrier).
-template <int NS>
-__device__ __forceinline__ void hist_flush(HistCache<NS>& hc, const Desc* desc) {
-    for (int i = threadIdx.x; i < NS; i += blockDim.x) {
-        const unsigned long long key = hc.key[i];
-        if (key == EMPTY_KEY) continue;
-        const Desc& D = desc[(uint32_t)(key >> 32)];
-        const uint32_t line = (uint32_t)key;
-        for (int c = 0; c < NCNT; ++c) {
-            const unsigned long long v = hc.cnt[i][c];
-            if (v) g_add((uint64_t*)&D.hist[(size_t)cache_to_hist(c) * D.L + line], v);
+// ---- line caches
+//
+// One workgroup's counters in LDS, a table per kind of event, so that a slot
+// holds only the counters its kind adds to: samples (Python bytes, growth and
+// shrink bytes, growth count | shrink count << 32, a trace having fewer than
+// 2^32 events; the native bytes are growth - shrink - Python), copies (exact
+// and sampled bytes) with timers (delays and events), tracked samples
+// (mallocs, frees).  Keys are (trace << 32) | line; K is a power of two below
+// 2^16.  A line may sit in either slot of a pair (one 16-byte read), and one
+// that finds both taken goes to global atomics.  Those are what the emit pass
+// waits on: of its 4.2 ms over 500 M events on 1 M lines, 1.9 went to the
+// copy and timer counters (a tenth of the events), most of which missed a
+// cache of 128 slots of 12 counters.
+template <int K, int V>
+struct LineTable {
+    alignas(16) unsigned long long key[K];
+    unsigned long long v[V][K];
+    __device__ __forceinline__ void init() {
+        for (int i = threadIdx.x; i < K; i += blockDim.x) {
+            key[i] = EMPTY_KEY;
+            for (int c = 0; c < V; ++c) v[c][i] = 0;
         }
     }
+    // the slot of a line, -1 if both of its slots hold others (a first slot
+    // once taken stays so: a line never comes to hold both)
+    __device__ __forceinline__ int find(uint32_t t, uint32_t line) {
+        const unsigned long long want = ((unsigned long long)t << 32) | line;
+        const uint32_t h = (line * 2654435761u) ^ (t * 0x9E3779B9u);
+        const int s0 = (int)(h >> 16) & (K - 2);
+        const ulonglong2 k = *(const ulonglong2*)&key[s0];
+        if (k.x == want) return s0;
+        if (k.y == want) return s0 + 1;
+        if (k.x == EMPTY_KEY) {
+            const unsigned long long o = atomicCAS(&key[s0], EMPTY_KEY, want);
+            if (o == EMPTY_KEY || o == want) return s0;
+        }
+        if (k.y == EMPTY_KEY) {
+            const unsigned long long o = atomicCAS(&key[s0 + 1], EMPTY_KEY, want);
+            if (o == EMPTY_KEY || o == want) return s0 + 1;
+        }
+        return -1;
+    }
+    __device__ __forceinline__ void add(int slot, int c, uint64_t x) {
+        if (x) atomicAdd(&v[c][slot], (unsigned long long)x);
+    }
+};
+enum { LS_PY = 0, LS_GB, LS_SB, LS_N, LA_BYTES = 0, LA_N, LK_M = 0, LK_F };
+constexpr uint32_t TIMER_LINE = 1u << 31;  // added to the trace in a timer's key
+
+template <class C>
+struct LineCaches {
+    LineTable<C::SAMPLES, 4> smp;
+    LineTable<C::AUX, 2> aux;
+};
+
+__device__ __forceinline__ void hist_global(const Desc& D, int h, uint32_t line, uint64_t x) {
+    if (x) g_add((uint64_t*)&D.hist[(size_t)h * D.L + line], x);
+}
+
+// A sample of py and nat bytes at line (their sum is not 0).
+template <class C>
+__device__ __forceinline__ void count_sample(C& c, const Desc& D, uint32_t t, uint32_t line, int64_t py, int64_t nat) {
+    const int64_t dl = py + nat;
+    const bool gr = dl > 0;
+    const uint64_t bytes = (uint64_t)(gr ? dl : -dl);
+    const int s = c.smp.find(t, line);
+    if (s >= 0) {
+        c.smp.add(s, LS_PY, (uint64_t)py);
+        c.smp.add(s, gr ? LS_GB : LS_SB, bytes);
+        c.smp.add(s, LS_N, gr ? 1ull : 1ull << 32);
+    } else {
+        hist_global(D, H_PY, line, (uint64_t)py);
+        hist_global(D, H_NAT, line, (uint64_t)nat);
+        hist_global(D, gr ? H_GN : H_SN, line, 1);
+        hist_global(D, gr ? H_GB : H_SB, line, bytes);
+    }
+}
+
+// A copy of x bytes or a timer event of delay x.
+template <class C>
+__device__ __forceinline__ void count_aux(C& c, const Desc& D, uint32_t t, uint32_t line, bool timer, uint64_t x) {
+    const int s = c.aux.find(timer ? t | TIMER_LINE : t, line);
+    if (s >= 0) {
+        c.aux.add(s, LA_BYTES, x);
+        if (timer) c.aux.add(s, LA_N, 1);
+    } else {
+        hist_global(D, timer ? H_NT : H_CE, line, x);
+        if (timer) hist_global(D, H_PT, line, (uint64_t)D.q);
+    }
+}
+
+// Copy samples of x bytes in all.
+template <class C>
+__device__ __forceinline__ void count_copy_sample(C& c, const Desc& D, uint32_t t, uint32_t line, uint64_t x) {
+    const int s = c.aux.find(t, line);
+    if (s >= 0)
+        c.aux.add(s, LA_N, x);
+    else
+        hist_global(D, H_CS, line, x);
+}
+
+__device__ __forceinline__ void count_tracked(LineTable<TRACK_SLOTS, 2>& c, const Desc& D, uint32_t t, uint32_t line,
+                                              uint32_t freed) {
+    const int s = c.find(t, line);
+    if (s >= 0) {
+        c.add(s, LK_M, 1);
+        c.add(s, LK_F, freed);
+    } else {
+        hist_global(D, H_LEAK_M, line, 1);
+        hist_global(D, H_LEAK_F, line, freed);
+    }
+}
+
+// Move a table to the per-line histograms (whole workgroup, after a barrier):
+// add(trace, line, slot) for each slot held.
+template <int K, int V, class A>
+__device__ __forceinline__ void flush_table(const LineTable<K, V>& c, A add) {
+    for (int i = threadIdx.x; i < K; i += blockDim.x) {
+        const unsigned long long k = c.key[i];
+        if (k != EMPTY_KEY) add((uint32_t)(k >> 32), (uint32_t)k, i);
+    }
+}
+
+template <class C>
+__device__ __forceinline__ void flush_lines(const C& c, const Desc* desc) {
+    flush_table(c.smp, [&](uint32_t t, uint32_t line, int i) {
+        const Desc& D = desc[t];
+        const uint64_t py = c.smp.v[LS_PY][i], gb = c.smp.v[LS_GB][i], sb = c.smp.v[LS_SB][i], n = c.smp.v[LS_N][i];
+        hist_global(D, H_PY, line, py);
+        hist_global(D, H_NAT, line, gb - sb - py);
+        hist_global(D, H_GN, line, n & 0xFFFFFFFFull);
+        hist_global(D, H_SN, line, n >> 32);
+        hist_global(D, H_GB, line, gb);
+        hist_global(D, H_SB, line, sb);
+    });
+    flush_table(c.aux, [&](uint32_t t, uint32_t line, int i) {
+        const Desc& D = desc[t & ~TIMER_LINE];
+        const bool timer = (t & TIMER_LINE) != 0;
+        const uint64_t x = c.aux.v[LA_BYTES][i], n = c.aux.v[LA_N][i];
+        hist_global(D, timer ? H_NT : H_CE, line, x);
+        hist_global(D, timer ? H_PT : H_CS, line, timer ? n * (uint64_t)D.q : n);
+    });
 }
 
 // last trace whose first segment index is <= x
@@ -3490,26 +3563,34 @@ __global__ __launch_bounds__(TILE) void k_bscan(const Desc* __restrict__ desc, i
 // One wave per segment (grid-stride): write the segment's samples with their
 // attribution, per-line counters, tracked samples and the frees that reclaim
 // them.
-constexpr int STAGE = 128;  // staged sample records per wave
-// The emit pass: four waves per workgroup around one line cache (30 KB of
-// LDS) and at most 96 VGPRs, so five waves share each SIMD.
-constexpr int EMIT_WAVES = 4;
-constexpr int EMIT_BLOCK = EMIT_WAVES * 64;
+// What a wave collects before it writes it out or adds it to the line tables,
+// up to 64 at a time: a window holds a few samples, copies and timers, and one
+// by one they would keep a few lanes busy each time.
+struct Staging {
+    Sample smp[64];
+    uint64_t ax[64];  // copies and timers: bytes or delay, bit 63: timer
+    uint32_t aline[64];
+};
 
 // Write staged samples [0, cnt) (cnt <= 64) to ranks r0.. and add them to
 // their lines' counters, one sample per lane.
-__device__ __forceinline__ void flush_stage(const Desc& D, uint32_t t, const Sample* stg, int cnt, int64_t r0,
-                                            HistCache<EMIT_SLOTS>& hc) {
+template <class C>
+__device__ __forceinline__ void flush_stage(const Desc& D, uint32_t t, const Sample* stg, int cnt, int64_t r0, C& hc) {
     const int l = lane_id();
     if (l < cnt && r0 + l < (int64_t)D.n) {
         const Sample smp = stg[l];
         store_sample(D.samples + r0 + l, smp);
-        if (smp.line < D.L) {
-            const int64_t dl = smp.py + smp.nat;
-            const bool gr = dl > 0;
-            hist_add(hc, D, t, smp.line, C_PY, smp.py, C_NAT, smp.nat, gr ? C_GN : C_SN, 1, gr ? C_GB : C_SB,
-                     gr ? dl : -dl);
-        }
+        if (smp.line < D.L) count_sample(hc, D, t, smp.line, smp.py, smp.nat);
+    }
+}
+
+// Add staged copies and timers [0, cnt) (cnt <= 64) to their lines' counters.
+template <class C>
+__device__ __forceinline__ void flush_aux(const Desc& D, uint32_t t, const Staging& sg, int cnt, C& hc) {
+    const int l = lane_id();
+    if (l < cnt) {
+        const uint64_t x = sg.ax[l];
+        count_aux(hc, D, t, sg.aline[l], (x >> 63) != 0, x & ~(1ull << 63));
     }
 }
 
@@ -3558,8 +3639,9 @@ __device__ __forceinline__ void emit_fetch_meta(const Desc& D, int64_t j, EmitIn
 // next segment sn is loaded into in as this one is consumed: its planes at
 // the start, its records window by window as each window's registers free up
 // (so the next segment's loads are in flight while this one computes).
-__device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, const EmitSeg& s, HistCache<EMIT_SLOTS>& hc,
-                                             Sample* stg, EmitIn& in, bool hn, const EmitSeg& sn) {
+template <class C>
+__device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, const EmitSeg& s, C& hc, Staging& sg,
+                                             EmitIn& in, bool hn, const EmitSeg& sn) {
     const int l = lane_id();
     const int t = s.t;
     const Desc& D = desc[t];
@@ -3605,8 +3687,9 @@ __device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, cons
     int64_t hwm = hh ? hv : 0;
     int64_t cF = 0, cP = 0;
     // Sample records are staged in LDS in rank order and written (with their
-    // per-line counters) 64 at a time, all lanes busy.
-    int staged = 0;
+    // per-line counters) up to 64 at a time; copies and timers likewise.
+    Sample* stg = sg.smp;
+    int staged = 0, aux = 0;
     int64_t stage_rank = base;
     // Window by window: decode and scan (prefixes stay in registers), then
     // the window's samples and frees.
@@ -3624,6 +3707,11 @@ __device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, cons
         cP = readlane64(p, 63);
         const uint64_t fm = ballot(dm < 0);
         const uint64_t m = wm[w];
+        if (staged + __popcll(m) > 64) {
+            flush_stage(D, (uint32_t)t, stg, staged, stage_rank, hc);
+            stage_rank += staged;
+            staged = 0;
+        }
         if (m != 0 || (fm != 0 && cur_has)) {
             const uint32_t pt = in.q[w].z, wline = in.q[w].w;
             const uint64_t below = m & lanemask_lt();
@@ -3701,44 +3789,67 @@ __device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, cons
             const bool lok = k < nv && line < D.L;
             const bool cp = lok && kind == 1u && r0 < (uint64_t)MAX_ABS_DELTA;
             const bool tm = lok && kind == 2u && (r0 >> 32) == 0;
-            if (ballot(cp || tm)) {
-                int64_t vcs = 0;  // bytes of the copy samples this event triggers
-                if (csmp) {
-                    const int64_t dc = cp ? (int64_t)r0 : 0;
-                    const int64_t sc_ = wave_incl_sum(dc) + cc;
-                    cc = readlane64(sc_, 63);
-                    const uint64_t cout = (uint64_t)sc_, cin = cout - (uint64_t)dc;
-                    const uint64_t nsmp = D.tc_shift >= 0 ? (cout >> D.tc_shift) - (cin >> D.tc_shift)
-                                                          : cout / (uint64_t)D.Tc - cin / (uint64_t)D.Tc;
-                    vcs = (int64_t)(nsmp * (uint64_t)D.Tc);
-                }
-                if (cp || tm)
-                    hist_add(hc, D, (uint32_t)t, line, cp ? C_CS : C_PT, cp ? vcs : D.q, cp ? C_CE : C_NT, (int64_t)r0,
-                             -1, 0, -1, 0);
+            if (csmp) {
+                const int64_t dc = cp ? (int64_t)r0 : 0;
+                const int64_t sc_ = wave_incl_sum(dc) + cc;
+                cc = readlane64(sc_, 63);
+                const uint64_t cout = (uint64_t)sc_, cin = cout - (uint64_t)dc;
+                const uint64_t nsmp = D.tc_shift >= 0 ? (cout >> D.tc_shift) - (cin >> D.tc_shift)
+                                                      : cout / (uint64_t)D.Tc - cin / (uint64_t)D.Tc;
+                if (cp && nsmp) count_copy_sample(hc, D, (uint32_t)t, line, nsmp * (uint64_t)D.Tc);
             }
+            const uint64_t am = ballot(cp || tm);
+            const int na = __popcll(am);
+            if (aux + na > 64) {
+                flush_aux(D, (uint32_t)t, sg, aux, hc);
+                aux = 0;
+            }
+            if (cp || tm) {
+                const int at = aux + __popcll(am & lanemask_lt());
+                sg.ax[at] = tm ? r0 | 1ull << 63 : r0;
+                sg.aline[at] = line;
+            }
+            aux += na;
         }
         // this window's registers take the next segment's window w (after
         // their last use here, so no copies and no early wait)
         if (hn) emit_load_record(record_addr(nbase, sn.nv, w), w, in);
-        if (staged >= 64) {
-            flush_stage(D, (uint32_t)t, stg, 64, stage_rank, hc);
-            stage_rank += 64;
-            staged -= 64;
-            Sample rest;
-            if (l < staged) rest = stg[64 + l];
-            if (l < staged) stg[l] = rest;
-        }
     }
     if (staged) flush_stage(D, (uint32_t)t, stg, staged, stage_rank, hc);
+    if (aux) flush_aux(D, (uint32_t)t, sg, aux, hc);
     if (err && l == 0) g_or32(&D.scal->err, err);
 }
 
-__global__ __launch_bounds__(EMIT_BLOCK) __attribute__((amdgpu_waves_per_eu(5))) void k_emit(
+// The emit pass's two shapes: waves per workgroup, waves per SIMD, slots of
+// the line tables.
+//
+// Wide, two workgroups per CU: a long single trace.  Its segments go to all
+// workgroups alike, so each of them meets every line, and the tables want to
+// be large.  Measured against four waves around one table of 128 slots with
+// 12 counters, five workgroups per CU: 500 M events with copies and timers on
+// 1 M lines 2.7-2.9 ms (4.1-4.3), 20 M on 100,000 lines 0.127 (0.25), 10 M
+// without them 0.069 (0.075), 100 M without 0.55-0.57 (0.54-0.57, bound by
+// the records).  16 waves, one workgroup per CU: 0.116 at 20 M, but
+// 0.56-0.58 at 100 M and 3.05 ms at 500 M.  Ten waves (five per SIMD): 0.142
+// and 0.62.
+// Narrow, five workgroups per CU: batches, whose workgroups meet the lines of
+// one or two traces, and short traces (see emit_wide).  1,024 traces of 1e3 to
+// 1e6 events 1.35 ms (1.44); 16 traces of 2 M events with
+// copies on 100 lines 0.24 (0.26), the wide shape 0.27; 2 of 10 M 0.20 (0.33).
+// Four workgroups per CU with 512 slots for samples: 1.2 ms for the 1,024
+// traces, but 0.28-0.33 for the 16.
+struct EmitWide { static constexpr int WAVES = 8, PER_SIMD = 4, SAMPLES = 512, AUX = 1024; };
+struct EmitNarrow { static constexpr int WAVES = 4, PER_SIMD = 5, SAMPLES = 256, AUX = 256; };
+
+template <class SHAPE>
+__global__ __launch_bounds__(64 * SHAPE::WAVES) __attribute__((amdgpu_waves_per_eu(SHAPE::PER_SIMD))) void k_emit(
     const Desc* __restrict__ desc, int ntraces, uint64_t nseg_total, uint64_t* ts) {
     stamp(ts);
-    __shared__ HistCache<EMIT_SLOTS> hc;
-    __shared__ Sample stage[EMIT_WAVES][STAGE];
-    hist_init(hc);
+    constexpr int EMIT_WAVES = SHAPE::WAVES;
+    __shared__ LineCaches<SHAPE> hc;
+    __shared__ Staging stage[EMIT_WAVES];
+    hc.smp.init();
+    hc.aux.init();
     __syncthreads();
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
     // A batch of several traces: each workgroup takes one contiguous run of
@@ -3788,7 +3899,7 @@ __global__ __launch_bounds__(EMIT_BLOCK) __attribute__((amdgpu_waves_per_eu(5)))
         }
     }
     __syncthreads();
-    hist_flush(hc, desc);
+    flush_lines(hc, desc);
 }
 
 // ----------------------------------------------------------------- clearing
@@ -3877,10 +3988,10 @@ __device__ bool count_lookback(const uint64_t* st, int64_t b, uint64_t& excl, un
 __global__ __launch_bounds__(256) void k_track(const Desc* __restrict__ desc, int ntraces, uint64_t nblk_total,
                                                unsigned long long* ctl, uint64_t* ts) {
     stamp(ts);
-    __shared__ HistCache<TRACK_SLOTS> hc;
+    __shared__ LineTable<TRACK_SLOTS, 2> hc;
     __shared__ uint64_t s_excl;
     __shared__ uint64_t w_cnt[4];
-    hist_init(hc);
+    hc.init();
     __syncthreads();
     const int tid = threadIdx.x, l = lane_id(), wv = tid >> 6;
     constexpr int PER = CBLK_WORDS / 256;  // each thread owns PER consecutive words
@@ -3977,13 +4088,17 @@ __global__ __launch_bounds__(256) void k_track(const Desc* __restrict__ desc, in
                 tq[4 * hh + 1] = line;
                 tq[4 * hh + 2] = ptr[u];
                 tq[4 * hh + 3] = freed;
-                if (line < D.L) hist_add(hc, D, t, line, C_LM, 1, C_LF, (int64_t)freed, -1, 0, -1, 0);
+                if (line < D.L) count_tracked(hc, D, t, line, freed);
             }
         }
         __syncthreads();  // w_cnt and s_excl are reused by the next block
     }
     __syncthreads();
-    hist_flush(hc, desc);
+    flush_table(hc, [&](uint32_t t, uint32_t line, int i) {
+        const Desc& D = desc[t];
+        hist_global(D, H_LEAK_M, line, hc.v[LK_M][i]);
+        hist_global(D, H_LEAK_F, line, hc.v[LK_F][i]);
+    });
 }
 
 // ------------------------------------------------ leak likelihood per line
@@ -4085,7 +4200,10 @@ static int occupancy_grid(const void* fn, int block) {
 }
 
 int chain_grid_limit() { return occupancy_grid((const void*)k_chain, BLOCK); }
-int emit_grid_limit() { return occupancy_grid((const void*)k_emit, EMIT_BLOCK); }
+int emit_grid_limit(bool wide) {
+    return wide ? occupancy_grid((const void*)k_emit<EmitWide>, 64 * EmitWide::WAVES)
+                : occupancy_grid((const void*)k_emit<EmitNarrow>, 64 * EmitNarrow::WAVES);
+}
 // workgroups of k_track the device holds at once (its look-back needs all of them resident)
 int track_grid_limit() { return occupancy_grid((const void*)k_track, 256); }
 
@@ -4121,9 +4239,14 @@ hipError_t launch_pass(int pass, const Desc* desc, int ntraces, uint64_t nseg_to
         case 2: k_chain<<<dim3(pgrid), dim3(BLOCK), 0, s>>>(desc, ntraces, nseg_total, ts); break;
         case 3: k_bscan<<<dim3((unsigned)ntile_total), dim3(TILE), 0, s>>>(desc, ntraces, ntile_total, ctl, ts); break;
         default: {
-            const uint64_t ewgs = (nseg_total + EMIT_WAVES - 1) / EMIT_WAVES;
-            const unsigned egrid = (unsigned)(ewgs < (uint64_t)grid_limit ? ewgs : (uint64_t)grid_limit);
-            k_emit<<<dim3(egrid), dim3(EMIT_BLOCK), 0, s>>>(desc, ntraces, nseg_total, ts);
+            const bool wide = emit_wide(ntraces, nseg_total);
+            const uint64_t ew = wide ? EmitWide::WAVES : EmitNarrow::WAVES;
+            const uint64_t ewgs = (nseg_total + ew - 1) / ew;
+            const dim3 egrid((unsigned)(ewgs < (uint64_t)grid_limit ? ewgs : (uint64_t)grid_limit)), eblock(64 * (unsigned)ew);
+            if (wide)
+                k_emit<EmitWide><<<egrid, eblock, 0, s>>>(desc, ntraces, nseg_total, ts);
+            else
+                k_emit<EmitNarrow><<<egrid, eblock, 0, s>>>(desc, ntraces, nseg_total, ts);
             break;
         }
     }
