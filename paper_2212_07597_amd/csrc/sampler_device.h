@@ -65,6 +65,11 @@ enum {
     NSPLANE
 };
 constexpr int64_t BFL_CHAIN = 8;
+// The chain pass's segments keep their largest sampled footprint, flag
+// BFL_PEAK, in a plane of the scan pass's, which reads it before it writes.
+constexpr int64_t BFL_PEAK = 4;
+constexpr int SP_BPK = SP_XCNT;
+static_assert(SP_XCNT == SP_BCNT + 6, "the chain pass writes seven planes in a row");
 
 // Look-back status words of one tile (each: 2-bit state | 62-bit payload,
 // written once per run; stored plane by plane like the segment values).
