@@ -270,9 +270,10 @@ SMP_API int sampler_last_counters(smp_sampler_t *s, uint64_t *out32);
  *   chain_cap  : distinct chains the summary pass follows through a segment
  *                before it gives up and leaves the segment to be followed
  *                from its actual entry (1..64, default 16)
- *   chain_grid : workgroups of the chain pass (0 = as many as the device
- *                holds at once, the default)
- *   emit_grid  : workgroups of the emit pass (0 = the same default)
+ *   chain_grid : workgroups of the chain pass (0 = three times as many as
+ *                the device holds at once)
+ *   emit_grid  : workgroups of the emit pass (0 = as many as the device
+ *                holds at once, for a batch of many traces a multiple)
  *   graphs     : 1 (default) = a run slot replays a launch sequence whose
  *                shape (trace count, segment, tile, block and line totals,
  *                grids, timing events) it launched before as a HIP graph,

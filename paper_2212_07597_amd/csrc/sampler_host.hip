@@ -428,7 +428,11 @@ int sampler_create(int device, void* hip_stream, uint64_t mem_budget, void* work
             return SMP_EDEVICE;
         }
     }
-    s->grid_chain = chain_grid_limit();
+    // Three rounds of the chain pass's workgroups even out the segments left to
+    // it, which come in clusters (one and three rounds: 1,024 traces of 1e3-1e6
+    // events 553 and 468 us, one of 1e8 65 and 58, one of 2e7 113 and 96, 256 of
+    // 1e5 56 and 57).
+    s->grid_chain = 3 * chain_grid_limit();
     s->grid_emit = emit_grid_limit(false);
     s->grid_emit_wide = emit_grid_limit(true);
     s->grid_track = track_grid_limit();
@@ -595,7 +599,17 @@ int run(smp_sampler_t* s, int blocking) {
         }
         key.ev_mask = s->pass_events;
         key.chain_grid = s->tuning.chain_grid ? s->tuning.chain_grid : (uint64_t)s->grid_chain;
-        key.emit_grid = s->tuning.emit_grid ? s->tuning.emit_grid : (uint64_t)s->grid_emit;
+        // A batch's emit workgroups each take one run of segments.  Up to four
+        // runs per trace, in whole rounds of the workgroups that the GPU holds
+        // (1,280), let most of them see the lines of one trace only, which
+        // their tables hold.  The emit pass with one round and by this rule:
+        // 1,024 traces of 1e3-1e6 events 1.35 and 1.02 ms, 2,000 of 20,000
+        // events 664 and 425 us.  Below two rounds' worth of traces more
+        // workgroups only fill and flush more tables: 2 traces of 1e7 events
+        // 177 us in one round and 214 in two, 64 of 200,000 112 and 125, 400
+        // of 50,000 161 and, with 1,600 workgroups, 187.
+        key.emit_grid = s->tuning.emit_grid ? s->tuning.emit_grid
+                                            : s->grid_emit * std::max<uint64_t>(1, 4 * cnt / s->grid_emit);
         // (the wide shape's workgroups are larger: no more of them than the GPU holds)
         if (emit_wide((int)cnt, key.seg)) key.emit_grid = std::min(key.emit_grid, (uint64_t)s->grid_emit_wide);
         key.track_grid = (uint64_t)s->grid_track;
