@@ -26,7 +26,7 @@ def sampler():
 
 def check(sampler, cases):
     import paper_2212_07597_amd as smp
-    print("line caches:", [c[0] for c in cases], flush=True)
+    print("line caches:", len(cases), cases[0][0], flush=True)
     ids = [sampler.submit_trace(ev, smp.make_params(kw["threshold"], kw["num_lines"], kw["copy_threshold"]))
            for _, ev, kw in cases]
     sampler.run(blocking=True)
@@ -46,4 +46,16 @@ def test_counters(sampler, lines, aux):
                           dict(threshold=T, num_lines=lines, copy_threshold=100_003)))
     for c in cases:
         check(sampler, [c])
+    check(sampler, cases)
+
+
+@pytest.mark.parametrize("count", [319, 640, 1300])
+def test_many_traces(sampler, count):
+    """Runs of segments per trace: one round of workgroups, two, several."""
+    ev = tg.mix(400, 20_000, num_lines=300, copy_frac=0.1, timer_frac=0.02)
+    cases = []
+    for i in range(count):
+        n = [SEG - 1, 3 * SEG, 5 * SEG + 1, 9 * SEG + 17, 1][i % 5]
+        cases.append((f"{count} traces, {i}", ev[i:i + n],
+                      dict(threshold=tg.MiB // (1 << i % 4), num_lines=300, copy_threshold=100_003)))
     check(sampler, cases)
