@@ -13,7 +13,7 @@ waited for, are reported beside it (config.serialized).
 
 Prints one JSON line with events/s, the roofline figures of the dominant
 kernel (the slowest of the five sampling passes; its algorithmic bytes are
-the 24-byte record of every event, over that kernel's own HIP-event duration
+the 24-byte record of every event, over that kernel's own device-clock duration
 in the serialized steps), the whole launch against the same bytes, and the
 CPU oracle timed on one pinned host core as a baseline.  The per-pass
 breakdown (pass_ms, kernel_ms) comes from untimed steps that record the
@@ -229,9 +229,9 @@ def main():
         release(step())
     torch.cuda.synchronize()
 
-    # Per-pass breakdown (untimed): events around every pass.  It names the
-    # dominant pass; the timed loop then records only the two events around
-    # that pass.
+    # Per-pass breakdown (untimed): times around every pass.  It names the
+    # dominant pass; the timed loop then records only the two around that
+    # pass.
     pass_ms, main_list, launch_list = [], [], []
     for _ in range(max(args.warmup, 3)):
         tid = step()

@@ -12,7 +12,7 @@ one parameter at a time, keeps the fastest, and caches the choice in a JSON
 file keyed by (GPU architecture, compute-unit count, size class), so a later
 process with the same key skips the search.
 
-The timing is the sampler's own: the HIP events around the five sampling
+The timing is the sampler's own: the device-clock time of the five sampling
 passes of the last run (``Sampler.last_timing``), the median of ``reps``
 runs per candidate.
 """
