@@ -258,9 +258,9 @@ __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(4))) vo
         if (k != NO_LINE && c.cnt[i]) g_add((uint64_t*)&counts[k], c.cnt[i]);
     }
     // The last workgroup to finish writes the status and the total.  (What the
-    // others wrote went to memory by agent-scope atomics: complete once this
-    // fence has waited for them, with no cache to write back.)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    // others wrote went to memory by agent-scope atomics, with no cache to
+    // write back: each wave waits for its own before the barrier.)
+    stores_done();
     __syncthreads();
     if (tid == 0) s_last = g_add_rtn(hdr + RH_DONE, 1ull);
     __syncthreads();

@@ -156,6 +156,11 @@ struct CopyOut {
     uint64_t at[3];
 };
 
+// Wait until the wave's stores and atomics so far are in memory, before a word
+// that tells another workgroup so.  (A release fence of workgroup scope
+// compiles to no such wait: it orders LDS only.)
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ---- wave64 helpers -------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
