@@ -45,3 +45,27 @@ def test_errors_in_the_last_tile(n):
     check(big, 1 << 20, 20, f"overflow n={n}")
     big["line"][5] = 99
     check(big, 1 << 20, 20, f"malformed and overflow n={n}")
+
+
+@pytest.mark.parametrize("n,size", [(GROW + 3 * LARGE, LARGE), (GROW, SMALL)])
+def test_volumes_past_64_bits_in_a_tile(n, size):
+    """Tiles whose volume is 2^64 and a little more (2^63 for the small ones),
+    or 2^65 and a little less; first, in the middle and the last whole one."""
+    ev = tg.mix(4, n, num_lines=20)
+    last = n // size - 1
+    for tile in (0, last // 2, last):
+        for d in ((1 << 51), (1 << 51) + 12_345, (1 << 51) + (1 << 49) - 1, (1 << 52) - 1):
+            big = ev.copy()
+            big["delta"][tile * size:(tile + 1) * size] = np.where(np.arange(size) % 2 == 0, 1, -1) * d
+            big["flags"][tile * size:(tile + 1) * size] = 0
+            assert oracle.rate(big, 1 << 20, 20)[0] == oracle.EOVERFLOW
+            check(big, 1 << 20, 20, f"n={n} tile {tile} delta {d}")
+    # the largest total that still counts (2^62 - 1) and the smallest that does not, in one tile and spread out
+    for at in (np.arange(1100), np.linspace(0, n - 1, 1100).astype(int)):
+        for total in ((1 << 62) - 1, 1 << 62):
+            edge = ev.copy()
+            edge["delta"], edge["flags"] = 0, 0
+            edge["delta"][at] = total // 1100
+            edge["delta"][at[:total % 1100]] += 1
+            assert int(edge["delta"].sum(dtype=np.uint64)) == total
+            check(edge, 1 << 40, 20, f"n={n} total {total}")
