@@ -28,6 +28,16 @@ inline bool emit_wide(int ntraces, uint64_t nseg) { return ntraces == 1 && nseg 
 constexpr uint64_t TILE_MAP_BYTES = 32768;  // map area per tile (in the tracked-list area)
 constexpr uint64_t TILE_MAP_ROOM = 163840;  // with the scratch of a tile's blocks
 
+// Segments of block b (64 segments) of a tile of nval segments: none past the
+// trace's end.
+constexpr int block_segments(int nval, int b) {
+    return nval <= b * 64 ? 0 : (nval - b * 64 < 64 ? nval - b * 64 : 64);
+}
+// The segment whose kept prefixes a block at segment j0 loads next: the first
+// of sims (bit i: segment j0 + i), or with none left the block's own first
+// (loaded, not used).  A block without segments has none to load.
+constexpr int64_t next_kept(int64_t j0, uint64_t sims) { return j0 + (sims ? __builtin_ctzll(sims) : 0); }
+
 constexpr int64_t MAX_ABS_DELTA = (int64_t)1 << 52;
 constexpr int64_t MAX_ABS_F = (int64_t)1 << 61;
 

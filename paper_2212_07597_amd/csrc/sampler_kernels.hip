@@ -2056,7 +2056,7 @@ __global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, in
         if (wv) return;
         fail = tmap_wide(D, k, nval, u_.wide, map);
     } else if (bad == 0) {
-        const int nb = nval - wv * 64 < 0 ? 0 : (nval - wv * 64 < 64 ? nval - wv * 64 : 64);
+        const int nb = block_segments(nval, wv);
         const int32_t rend = readlane32(Rv + (int32_t)af, 63);
         const TmapBlock mine = tmap_block(D, k, k * TILE + wv * 64, wv, nb, (int32_t)T, Rv, Sxv, Snv, rend, u_.blk[wv]);
         if (l == 0) s_blk[wv] = mine;
@@ -2260,6 +2260,8 @@ __device__ __forceinline__ int follow_groups(BlockLds& B, int32_t gx, int32_t gn
 // coordinates).
 __device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int nb, int32_t T, int kindv, int32_t Rv,
                                                 int32_t Sxv, int32_t Snv, int32_t kxv, int32_t rend, BlockLds& B) {
+    // (a block past the trace's end has no prefixes to load: every entry passes)
+    if (nb == 0) return BlockMap{1, 0, 0, 0, 0, 64, 0};
     const int l = lane_id();
     int32_t XA = 0, XB = 0;     // lane l: chains in columns l and 64 + l
     int idA = 0, idB = 0;
@@ -2273,7 +2275,7 @@ __device__ __forceinline__ BlockMap build_block(const Desc& D, int64_t j0, int n
     int32_t pf[NW];
     auto prefetch = [&](int s) {
         const uint64_t m = s < 64 ? simm & (~0ull << s) : 0;
-        load_kept32(D, j0 + (m ? ctz64(m) : 0), pf);
+        load_kept32(D, next_kept(j0, m), pf);
     };
     // segment s's prefixes (just prefetched) into LDS, and their group extremes
     int32_t gx = 0, gn = 0;
@@ -2732,7 +2734,7 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
         w_wide[wv] = nwide_w;
     }
     // whether this wave's 64 segments may get a block map (see there)
-    const int nb = nval - wv * 64 < 64 ? nval - wv * 64 : 64;
+    const int nb = block_segments(nval, wv);
     const int64_t bR = iF - af;
     int32_t bSx = 0, bSn = 0;
     {

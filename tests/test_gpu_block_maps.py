@@ -90,3 +90,23 @@ def test_still_segments(sampler):
     order = [shapes[i] for i in rng.integers(0, len(shapes), 300)]
     cases = [(f"still T{T}", trace(*order), dict(threshold=T, num_lines=5)) for T in (50, 100, 101, 150, 1000)]
     check(sampler, cases)
+
+
+@pytest.mark.parametrize("segments", [8, 9, 20, 63, 64, 65, 130])
+def test_workspace_without_room_to_spare(segments):
+    """A trace of a few blocks alone in a workspace of exactly its size."""
+    import paper_2212_07597_amd as smp
+    import torch
+    n = segments * SEG - 100
+    ev = tg.mix(85, n, num_lines=20)
+    dev = torch.from_numpy(ev.view(np.uint8)).to("cuda")
+    p = smp.make_params(2 * tg.MiB, 20)
+    with_room = smp.sampler_fixed_bytes() + smp.workspace_bytes(n, p, ev_on_device=True)
+    s = smp.Sampler(workspace=with_room)
+    try:
+        print("exact workspace:", segments, flush=True)
+        tid = s.submit_trace(dev, p)
+        s.run(blocking=True)
+        compare(s.fetch_profile(tid), oracle.run(ev, threshold=2 * tg.MiB, num_lines=20), f"{segments} segments")
+    finally:
+        s.close()
