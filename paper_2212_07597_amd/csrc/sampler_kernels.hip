@@ -1347,7 +1347,10 @@ __device__ int chain_maps(const Desc& D, int t0, int nt, unsigned long long* ctl
     int64_t nw[TC_CB][4], nh[TC_CB];
     load(t0, nw, nh);
     // tile 0's entry is 0, every other's the exit published before it
-    int64_t e = t0 ? unpack(readlaneu64(ld_status(ts.at(W_XF, t0 - 1)), 0)) : 0;
+    // (always there: the chain is freed after its exits are in memory)
+    const uint64_t before = t0 ? readlaneu64(ld_status(ts.at(W_XF, t0 - 1)), 0) : 0;
+    if (t0 && !wstate(before)) return 0;
+    int64_t e = t0 ? unpack(before) : 0;
     int t = t0;
     for (; t < nt;) {
         int64_t cw[TC_CB][4], ch[TC_CB];
@@ -1407,11 +1410,11 @@ __device__ int chain_maps(const Desc& D, int t0, int nt, unsigned long long* ctl
 __device__ void chain_done_tiles(const Desc& D, int64_t k, unsigned long long* ctl) {
     const int l = lane_id();
     const int nt = __builtin_amdgcn_readfirstlane((int)D.ntile);
-    // the map's words were stored through to memory: complete after this
-    // fence, as the mark is before the tile is counted
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    // the map's words are in memory before the mark is, and the mark before
+    // the tile is counted
+    stores_done();
     if (l == 0) st_status(D.blk + k, 1);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    stores_done();
     uint64_t done = 0;
     if (l == 0) done = g_add_rtn(&D.scal->tmap_done, 1ull);
     const bool last = readlaneu64(done, 0) == (uint64_t)nt - 1;
@@ -1440,7 +1443,7 @@ __device__ void chain_done_tiles(const Desc& D, int64_t k, unsigned long long* c
     }
     if (l == 0) __hip_atomic_store(gp(&D.scal->pad), (uint32_t)pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // the exits and the position are in memory before the chain is free
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    stores_done();
     if (l == 0) __hip_atomic_store(gp(&D.scal->reserved), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -2834,8 +2837,11 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
                 if (s_bm[b].one_from < 64) c = b;
             bool out = false;
             if (c >= 0) {
+                // a tile map may have published the exit already: it must agree
+                const uint64_t pw = D.tmap ? ld_status(ts.at(W_XF, k)) : 0;
                 int32_t x = __builtin_amdgcn_readfirstlane(u_.blk[c].ex[0]);
                 for (int b = c + 1; b < TWAVES; ++b) x = follow_block(b, x);
+                if (wstate(pw) && unpack(pw) != x && l == 0) g_or32(&D.scal->err, 4u);
                 st_status(ts.at(W_XF, k), pack(x, 1));
                 out = true;
             }
