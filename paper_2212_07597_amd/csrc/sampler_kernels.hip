@@ -64,7 +64,12 @@ struct LineTable {
     __device__ __forceinline__ int find(uint32_t t, uint32_t line) {
         const unsigned long long want = ((unsigned long long)t << 32) | line;
         const uint32_t h = (line * 2654435761u) ^ (t * 0x9E3779B9u);
-        const int s0 = (int)(h >> 16) & (K - 2);
+        // (the topmost bits, which a multiplicative hash spreads evenly over
+        // consecutive lines and which put a line's timers half a table from its
+        // copies: with bits 16 up, 64 lines' copies and timers overflowed 128
+        // pairs, and the emit pass on nine copies in ten events took 58 us
+        // instead of 22)
+        const int s0 = (int)(h >> (32 - __builtin_ctz(K))) & (K - 2);
         const ulonglong2 k = *(const ulonglong2*)&key[s0];
         if (k.x == want) return s0;
         if (k.y == want) return s0 + 1;
@@ -114,16 +119,18 @@ __device__ __forceinline__ void count_sample(C& c, const Desc& D, uint32_t t, ui
     }
 }
 
-// A copy of x bytes or a timer event of delay x.
+// A copy of x bytes that triggers copy samples of `sampled` bytes in all, or a
+// timer event of delay x.
 template <class C>
-__device__ __forceinline__ void count_aux(C& c, const Desc& D, uint32_t t, uint32_t line, bool timer, uint64_t x) {
+__device__ __forceinline__ void count_aux(C& c, const Desc& D, uint32_t t, uint32_t line, bool timer, uint64_t x,
+                                          uint64_t sampled) {
     const int s = c.aux.find(timer ? t | TIMER_LINE : t, line);
     if (s >= 0) {
         c.aux.add(s, LA_BYTES, x);
-        if (timer) c.aux.add(s, LA_N, 1);
+        c.aux.add(s, LA_N, timer ? 1 : sampled);
     } else {
         hist_global(D, timer ? H_NT : H_CE, line, x);
-        if (timer) hist_global(D, H_PT, line, (uint64_t)D.q);
+        hist_global(D, timer ? H_PT : H_CS, line, timer ? (uint64_t)D.q : sampled);
     }
 }
 
@@ -159,9 +166,36 @@ __device__ __forceinline__ void flush_table(const LineTable<K, V>& c, A add) {
     }
 }
 
+// The same with the held slots gathered first (list: room for K in LDS, n: a
+// word of LDS), so that a wave's 64 atomics of one counter go to 64 lines.  A
+// table of few lines sends its counters in the fewest requests then, and those
+// of all workgroups queue at the same few addresses: the emit pass on 12 M
+// events on 64 lines took 138 us slot by slot (512 workgroups of 512 slots)
+// and takes 68.
+template <int K, int V, class A>
+__device__ __forceinline__ void flush_gathered(const LineTable<K, V>& c, uint16_t* list, int* n, A add) {
+    __syncthreads();  // (list and n are free)
+    if (threadIdx.x == 0) *n = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < K; i += blockDim.x) {
+        const bool held = c.key[i] != EMPTY_KEY;
+        const uint64_t m = ballot(held);
+        int at = 0;
+        if (m && lane_id() == 0) at = atomicAdd(n, __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (held) list[at + __popcll(m & lanemask_lt())] = (uint16_t)i;
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < *n; x += blockDim.x) {
+        const int i = list[x];
+        const unsigned long long k = c.key[i];
+        add((uint32_t)(k >> 32), (uint32_t)k, i);
+    }
+}
+
 template <class C>
-__device__ __forceinline__ void flush_lines(const C& c, const Desc* desc) {
-    flush_table(c.smp, [&](uint32_t t, uint32_t line, int i) {
+__device__ __forceinline__ void flush_lines(const C& c, const Desc* desc, uint16_t* list, int* n) {
+    flush_gathered(c.smp, list, n, [&](uint32_t t, uint32_t line, int i) {
         const Desc& D = desc[t];
         const uint64_t py = c.smp.v[LS_PY][i], gb = c.smp.v[LS_GB][i], sb = c.smp.v[LS_SB][i], n = c.smp.v[LS_N][i];
         hist_global(D, H_PY, line, py);
@@ -171,7 +205,7 @@ __device__ __forceinline__ void flush_lines(const C& c, const Desc* desc) {
         hist_global(D, H_GB, line, gb);
         hist_global(D, H_SB, line, sb);
     });
-    flush_table(c.aux, [&](uint32_t t, uint32_t line, int i) {
+    flush_gathered(c.aux, list, n, [&](uint32_t t, uint32_t line, int i) {
         const Desc& D = desc[t & ~TIMER_LINE];
         const bool timer = (t & TIMER_LINE) != 0;
         const uint64_t x = c.aux.v[LA_BYTES][i], n = c.aux.v[LA_N][i];
@@ -3601,7 +3635,7 @@ __device__ __forceinline__ void flush_aux(const Desc& D, uint32_t t, const Stagi
     const int l = lane_id();
     if (l < cnt) {
         const uint64_t x = sg.ax[l];
-        count_aux(hc, D, t, sg.aline[l], (x >> 63) != 0, x & ~(1ull << 63));
+        count_aux(hc, D, t, sg.aline[l], (x >> 63) != 0, x & ~(1ull << 63), 0);
     }
 }
 
@@ -3800,6 +3834,7 @@ __device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, cons
             const bool lok = k < nv && line < D.L;
             const bool cp = lok && kind == 1u && r0 < (uint64_t)MAX_ABS_DELTA;
             const bool tm = lok && kind == 2u && (r0 >> 32) == 0;
+            uint64_t sampled = 0;  // bytes of the copy samples this event triggers
             if (csmp) {
                 const int64_t dc = cp ? (int64_t)r0 : 0;
                 const int64_t sc_ = wave_incl_sum(dc) + cc;
@@ -3807,20 +3842,28 @@ __device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, cons
                 const uint64_t cout = (uint64_t)sc_, cin = cout - (uint64_t)dc;
                 const uint64_t nsmp = D.tc_shift >= 0 ? (cout >> D.tc_shift) - (cin >> D.tc_shift)
                                                       : cout / (uint64_t)D.Tc - cin / (uint64_t)D.Tc;
-                if (cp && nsmp) count_copy_sample(hc, D, (uint32_t)t, line, nsmp * (uint64_t)D.Tc);
+                sampled = cp ? nsmp * (uint64_t)D.Tc : 0;
             }
             const uint64_t am = ballot(cp || tm);
             const int na = __popcll(am);
-            if (aux + na > 64) {
-                flush_aux(D, (uint32_t)t, sg, aux, hc);
-                aux = 0;
+            if (na >= 32) {
+                // a window of mostly such events keeps the lanes busy by
+                // itself (300,000 events, nine copies in ten: 21.7 us staged,
+                // 20.6 directly; 12 M: 142 and 138)
+                if (cp || tm) count_aux(hc, D, (uint32_t)t, line, tm, r0, sampled);
+            } else {
+                if (sampled) count_copy_sample(hc, D, (uint32_t)t, line, sampled);
+                if (aux + na > 64) {
+                    flush_aux(D, (uint32_t)t, sg, aux, hc);
+                    aux = 0;
+                }
+                if (cp || tm) {
+                    const int at = aux + __popcll(am & lanemask_lt());
+                    sg.ax[at] = tm ? r0 | 1ull << 63 : r0;
+                    sg.aline[at] = line;
+                }
+                aux += na;
             }
-            if (cp || tm) {
-                const int at = aux + __popcll(am & lanemask_lt());
-                sg.ax[at] = tm ? r0 | 1ull << 63 : r0;
-                sg.aline[at] = line;
-            }
-            aux += na;
         }
         // this window's registers take the next segment's window w (after
         // their last use here, so no copies and no early wait)
@@ -3909,8 +3952,9 @@ __global__ __launch_bounds__(64 * SHAPE::WAVES) __attribute__((amdgpu_waves_per_
             s = sn;
         }
     }
-    __syncthreads();
-    flush_lines(hc, desc);
+    __shared__ int held;
+    static_assert(sizeof(stage) >= 2 * SHAPE::SAMPLES && sizeof(stage) >= 2 * SHAPE::AUX, "a list of slots");
+    flush_lines(hc, desc, (uint16_t*)stage, &held);
 }
 
 // ----------------------------------------------------------------- clearing
