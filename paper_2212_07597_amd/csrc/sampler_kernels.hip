@@ -2202,11 +2202,30 @@ __global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, in
 // traces of 1e3-1e6 events at T = 256 KiB / 1 MiB / 10 MiB 1.12 -> 0.28 ms; a
 // trace of 777,777 events at T = 3 MiB (three tiles) 1.53 -> 0.15 ms; one of
 // 1.2e7 events at T = 10 MiB 9.5 -> 0.2 ms.  (Prefixes two segments ahead
-// instead of one: 25 spilled registers and 0.16 / 0.29 ms.)  A tile of few SIM segments
-// (below BM_MIN_SIM) walks them in less time than a block map takes.
+// instead of one: 25 spilled registers and 0.16 / 0.29 ms.) 
 constexpr int BM_SRC = 512;   // sources per block
 constexpr int BM_OPEN = 14;   // ~31 sources per segment on the log-uniform mixes while entries are left
-constexpr int BM_MIN_SIM = 8; // SIM segments of a tile below which the walk is short anyway
+//
+// Whether a tile takes them.  One that has to wait for its entry builds them
+// meanwhile (from BM_MIN_SIM SIM segments on: 700 segments, the last 188 of them
+// a tile of their own, T = 10 MiB, 140 us, and 242 with the second tile walked).
+// One whose entry is there compares the walk's time with the slowest block's, in
+// 1/20 us.  The walk stops in a SIM segment for the share of entries outside
+// its no-sample interval (expected stops, in 1/256), 1.25 us each, or 0.85 in a
+// sparse tile (see the resolve pass).  A block takes about 10 us, 1.55 per SIM
+// segment up to its first segment with a total map (its chains are many until
+// there) and 1.5 per stop after it.  Walked and mapped, us: traces of 64 / 128 /
+// 256 / 512 segments at T = 10 MiB 41 / 75 / 143 / 292 and 109 / 110 / 128 /
+// 138, at T = 3 MiB 73 / 142 / 280 / 550 and 104 / 105 / 108 / 129, at T = 1 MiB
+// 11 / 14 / 26 / 52 and 12 / 14 / 22 / 32; half copies at T = 1 MiB 36 / 73 /
+// 140 / 257 and 49 / 54 / 58 / 64, at T = 10 MiB (sparse) 19 / 31 / 57 / 106 and
+// 82 / 89 / 93 / 101.  At T = 30 MiB the walk takes 15 / 24 / 43 / 78, and a map
+// tried in vain 20 more.
+__device__ __forceinline__ int block_cost(int many, int after) { return 200 + 31 * many + 30 * after / 256; }
+__device__ __forceinline__ bool block_maps_pay(bool sparse, int stops, int slowest) {
+    return (sparse ? 17 : 25) * stops / 256 > slowest;
+}
+constexpr int BM_MIN_SIM = 8;
 constexpr int BM_PAR = 4;     // chains that stop in a segment from which they are searched side by side
 
 struct alignas(16) BlockLds {
@@ -2710,11 +2729,14 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     __shared__ int32_t s_bent[TWAVES + 1];
     __shared__ int r_ready[RING];  // walk-order SIM index held by each slot
     __shared__ int s_prod, s_cons, s_abort;
+    __shared__ int s_known;  // 1: the tile's entry is there already
     __shared__ int w_wide[TWAVES];
+    __shared__ int w_stops[TWAVES], w_cost[TWAVES];  // expected stops of the walk, cost of the block's map
     __shared__ int64_t s_entry;
     const int tid = threadIdx.x, wv = tid >> 6, l = lane_id();
     if (tid == 0) {
         s_tk = g_add_rtn((uint64_t*)&ctl[2], 1ull);
+        s_known = 1;
         s_prod = 0;
         s_cons = 0;
         s_abort = 0;
@@ -2730,6 +2752,8 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     const bool valid = j < ns;
     const int nval = (int)((ns - k * TILE) < TILE ? (ns - k * TILE) : TILE);  // valid lanes
     const StatusView ts{D.tstat, (int64_t)D.ntile};
+    // (a tile map may have published the previous tile's exit)
+    if (k > 0 && tid == 0) s_known = wstate(ld_status(ts.at(W_XF, k - 1))) != 0;
     const SMP_GLOBAL int64_t* sp = gp(D.seg) + (valid ? j : 0);
     int64_t af = 0, ap = 0, ac = 0, kf = 0, lo = 0, hi = 0, mxf = 0, mnf = 0;
     int kind = MAP_CONST, flg = 0;
@@ -2764,7 +2788,14 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     }
     // SIM maps whose no-sample interval holds at least half of the entries
     const int nwide_w = __popcll(ballot(valid && kind == MAP_SIM && hi - lo >= D.T));
+    // (see block_maps_pay)
+    const int first_tot = tot ? ctz64(tot) : 64;
+    const float inside = hi < lo ? 0.0f : (float)(hi - lo + 1) / (float)(2 * T - 1);
+    const int stop = valid && kind == MAP_SIM ? (int)(256.0f * (1.0f - (inside < 1.0f ? inside : 1.0f))) : 0;
+    const uint64_t stops = (uint64_t)wave_sum((int64_t)((uint64_t)stop << 32 | (uint64_t)(l > first_tot ? stop : 0)));
     if (l == 0) {
+        w_stops[wv] = (int)(stops >> 32);
+        w_cost[wv] = block_cost(__popcll(sim & range_mask(0, 0, first_tot)), (int)(uint32_t)stops);
         w_tot[wv] = tot;
         w_sim[wv] = sim;
         w_fit[wv] = fitm;
@@ -2842,7 +2873,12 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     // Block maps: the tile's eight blocks are followed for all entries at
     // once, one wave each; the tile's entry then costs eight lookups and the
     // segments' exits are read from the rows its chain left.
-    bool blocks = nsim >= BM_MIN_SIM;
+    int nstops = 0, slowest = 0;
+    for (int w = 0; w < TWAVES; ++w) {
+        nstops += w_stops[w];
+        slowest = w_cost[w] > slowest ? w_cost[w] : slowest;
+    }
+    bool blocks = s_known ? block_maps_pay(sparse, nstops, slowest) : nsim >= BM_MIN_SIM;
     for (int w = 0; w < TWAVES; ++w) blocks = blocks && s_bok[w] != 0;
     const bool tried = blocks;
     int32_t bref = 0;  // (BlockMap::ref)
