@@ -116,9 +116,9 @@ struct Scalars {
     uint64_t K;
     uint64_t H;
     uint32_t err;      // bit 0: malformed event, bit 1: overflow, bits 2-3: internal fault
-    uint32_t pad;        // tile maps: the tile the chain stands at
-    uint64_t tmap_done;  // tiles whose map is done
-    uint64_t reserved;   // 1 while a wave chains tiles
+    uint32_t tmap_pos;   // tile maps: the tile the chain stands at
+    uint64_t tmap_held;  // 1 while a wave chains tiles
+    uint64_t reserved;
 };
 
 // Per-trace descriptor, built by the host for every launch.

@@ -1435,50 +1435,42 @@ __device__ int chain_maps(const Desc& D, int t0, int nt, unsigned long long* ctl
     return t - t0;
 }
 
-// Chain what can be chained, by the wave that has just finished a tile's map:
-// tiles are marked as they are done (D.blk, which the tracked-list pass finds
-// cleared again), and whichever wave finds the chain free (Scalars::reserved)
-// takes it on from where it stands (Scalars::pad) over the marked tiles.  The
-// last tile's wave waits for the chain and finishes it.  So the chain runs
-// beside the builds (5e8 events, 1,908 tiles: 0.7 ms of it), not after them.
-__device__ void chain_done_tiles(const Desc& D, int64_t k, unsigned long long* ctl) {
+// Chain what can be chained, by the wave that has just written a tile's map:
+// it marks the tile (D.blk, cleared again by the resolve pass), and whichever
+// wave finds the chain free takes it on from where it stands over the marked
+// tiles.  A wave that finds it held leaves: the holder looks again after it has
+// freed the chain.  A tile without a map is never marked and ends the chain.
+// So the chain runs beside the builds (5e8 events, 1,908 tiles: 0.7 ms of it),
+// not after them, and no wave waits for another.
+__device__ void chain_mapped_tiles(const Desc& D, int64_t k, unsigned long long* ctl) {
     const int l = lane_id();
     const int nt = __builtin_amdgcn_readfirstlane((int)D.ntile);
-    // the map's words are in memory before the mark is, and the mark before
-    // the tile is counted
-    stores_done();
+    auto marked = [&](int pos) {  // tiles marked from pos on, without a gap
+        const int t = pos + l;
+        const uint64_t m = ballot(t < nt && ld_status(D.blk + (t < nt ? t : 0)) != 0);
+        return ~m ? ctz64(~m) : 64;
+    };
+    stores_done();  // the map is in memory before the mark
     if (l == 0) st_status(D.blk + k, 1);
-    stores_done();
-    uint64_t done = 0;
-    if (l == 0) done = g_add_rtn(&D.scal->tmap_done, 1ull);
-    const bool last = readlaneu64(done, 0) == (uint64_t)nt - 1;
-    Spin sp;
-    for (;;) {
+    int pos;
+    do {
+        stores_done();  // the mark (the freed chain) before the chain is asked for
         uint64_t held = 0;
         if (l == 0)
-            held = __hip_atomic_exchange(gp(&D.scal->reserved), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!readlaneu64(held, 0)) break;
-        if (!last || spin_abort(ctl, sp)) return;
-    }
-    int pos = readlane32((int)__hip_atomic_load(gp(&D.scal->pad), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0);
-    while (pos < nt) {
-        const int t = pos + l;
-        const uint64_t ready = ballot(t < nt && ld_status(D.blk + (t < nt ? t : 0)) != 0);
-        const int n = ~ready ? ctz64(~ready) : 64;
-        if (!n) break;
-        // drop stale copies of the tiles' words before they are read
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        const int c = chain_maps(D, pos, pos + n, ctl);
-        pos = c < n ? nt : pos + n;  // (a tile without a map ends the chain)
-    }
-    if (last) {
-        for (int i = l; i < nt; i += 64) st_status(D.blk + i, 0);
-        return;
-    }
-    if (l == 0) __hip_atomic_store(gp(&D.scal->pad), (uint32_t)pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // the exits and the position are in memory before the chain is free
-    stores_done();
-    if (l == 0) __hip_atomic_store(gp(&D.scal->reserved), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            held = __hip_atomic_exchange(gp(&D.scal->tmap_held), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (readlaneu64(held, 0)) return;
+        pos = readlane32((int)__hip_atomic_load(gp(&D.scal->tmap_pos), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0);
+        for (int n; pos < nt && (n = marked(pos)) > 0;) {
+            // drop stale copies of the tiles' words before they are read
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            pos = chain_maps(D, pos, pos + n, ctl) < n ? nt : pos + n;
+        }
+        if (l == 0)
+            __hip_atomic_store(gp(&D.scal->tmap_pos), (uint32_t)pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stores_done();  // the exits and the position before the chain is free
+        if (l == 0) __hip_atomic_store(gp(&D.scal->tmap_held), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stores_done();  // free before the marks are looked at again
+    } while (pos < nt && marked(pos) > 0);
 }
 
 // The map of a tile past the 32-bit range, by one wave over all its segments
@@ -2020,7 +2012,7 @@ __global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, in
     } u_;
     __shared__ TmapRuns pieces;  // the tile's map so far (runs not yet joined)
     __shared__ TmapBlock s_blk[TWAVES];
-    __shared__ int s_bad[TWAVES];  // 1: the tile does not qualify, 2: it needs the wide path
+    __shared__ int s_bad[TWAVES];  // not 0: the tile does not qualify, then: it needs the wide path
     __shared__ int64_t s_ext[3][TWAVES];  // each block's footprint change, largest and smallest footprint
     __shared__ int s_new[TWAVES];  // segments with a new extreme while entries are unsampled
     const int tid = threadIdx.x, l = lane_id();
@@ -2036,20 +2028,39 @@ __global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, in
     const bool valid = tid < nval;
     const SMP_GLOBAL int64_t* sp = gp(D.seg) + k * TILE + (valid ? tid : 0);
     // every segment SIM, with a no-sample interval of at least T entries
-    // (then max - min < T over its prefixes and the entry)
+    // (then max - min < T over its prefixes and the entry); a tile where one is
+    // not leaves after this one look (resolve pass of 1.2e7 events at T = 128 KiB
+    // without tile maps 18 us, with every tile of it marked and chained like a
+    // mapped one 27, like this 20)
+    const int64_t fl = sp[SP_FLG * ns];
+    {
+        const int64_t lo = sp[SP_LO * ns], hi = sp[SP_HI * ns];
+        const bool no = valid && ((fl & 3) != MAP_SIM || hi < lo || hi - lo < T - 1);
+        const int no_w = ballot(no) || !prefixes_kept(D) ? 1 : 0;
+        if (l == 0) s_bad[wv] = no_w;
+        __syncthreads();
+        int no_map = 0;
+        for (int w = 0; w < TWAVES; ++w) no_map |= s_bad[w];
+        if (no_map) {
+            if (tid == 0) {
+                map[TM_HDR] = TM_NONE;
+                g_add((uint64_t*)&ctl[6 + TMF_QUALIFY], 1ull);
+            }
+            return;
+        }
+        __syncthreads();  // (s_bad is written again)
+    }
     int64_t af = 0, mx = 0, mn = 0;
     int32_t Rv, Sxv, Snv;
     {
-        const int64_t lo = sp[SP_LO * ns], hi = sp[SP_HI * ns], fl = sp[SP_FLG * ns];
         if (valid) {
             af = sp[SP_AF * ns];
             mx = sp[SP_MXF * ns];
             mn = sp[SP_MNF * ns];
         }
-        const bool no = valid && ((fl & 3) != MAP_SIM || hi < lo || hi - lo < T - 1);
         const int64_t R = wave_incl_sum(af) - af;
         const bool in = R + mx < KEPT32 && R + mn > -KEPT32 && (fl & FLG_FIT);
-        const int bad = ballot(no) || !prefixes_kept(D) ? 1 : (ballot(valid && !in) || T >= KEPT32 ? 2 : 0);
+        const int bad = ballot(valid && !in) || T >= KEPT32 ? 2 : 0;
         const int64_t im = wave_incl_max(R + mx), in_ = wave_incl_min(R + mn);
         if (l == 63) {
             s_bad[wv] = bad;
@@ -2077,22 +2088,20 @@ __global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, in
     __syncthreads();
     int bad = 0, fresh_segs = 0;
     for (int w = 0; w < TWAVES; ++w) {
-        bad = bad == 1 || s_bad[w] == 1 ? 1 : (bad | s_bad[w]);
+        bad |= s_bad[w];
         fresh_segs += s_new[w];
     }
-    int fail = bad == 1 ? TMF_QUALIFY : 0;
+    int fail = 0;
     // A tile whose entries take too long to sample would start more chains
     // than a map holds (~31 sources per segment with a new extreme on the
     // log-uniform mixes, and then too many runs): found out here, not after
     // a build of 0.2 to 0.4 ms.
-    if (!fail && fresh_segs > TS_FRESH) {
-        bad = 1;
+    if (fresh_segs > TS_FRESH) {
         fail = TMF_SOURCES;
-    }
-    if (bad == 2) {
+    } else if (bad) {
         if (wv) return;
         fail = tmap_wide(D, k, nval, u_.wide, map);
-    } else if (bad == 0) {
+    } else {
         const int nb = block_segments(nval, wv);
         const int32_t rend = readlane32(Rv + (int32_t)af, 63);
         const TmapBlock mine = tmap_block(D, k, k * TILE + wv * 64, wv, nb, (int32_t)T, Rv, Sxv, Snv, rend, u_.blk[wv]);
@@ -2173,7 +2182,7 @@ __global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, in
         st_map(map + TM_HDR, fail ? TM_NONE : TM_MAPPED);
         g_add((uint64_t*)&ctl[fail ? 6 + fail : 5], 1ull);
     }
-    chain_done_tiles(D, k, ctl);
+    if (!fail) chain_mapped_tiles(D, k, ctl);
 }
 
 // ------------------------------------------------------------ block maps
@@ -2752,6 +2761,7 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     const bool valid = j < ns;
     const int nval = (int)((ns - k * TILE) < TILE ? (ns - k * TILE) : TILE);  // valid lanes
     const StatusView ts{D.tstat, (int64_t)D.ntile};
+    if (D.tmap && tid == 0) D.blk[k] = 0;  // (the mark of a tile map)
     // (a tile map may have published the previous tile's exit)
     if (k > 0 && tid == 0) s_known = wstate(ld_status(ts.at(W_XF, k - 1))) != 0;
     const SMP_GLOBAL int64_t* sp = gp(D.seg) + (valid ? j : 0);

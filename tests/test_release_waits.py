@@ -60,15 +60,18 @@ def test_rate_finish(tmp_path_factory, waves):
 
 
 def test_tile_map_chain(tmp_path_factory):
-    """A tile's map before its mark, the mark before the count of tiles done,
-    and the chain's exits and position before the chain is free."""
+    """A tile's map before its mark, the mark before the chain is asked for, the
+    chain's exits and position before it is free, and free before the marks are
+    read again."""
     body = kernel(tmp_path_factory, "sampler_kernels.hip", "6k_tmap")
-    count = only(body, r"global_atomic_add_x2 .* sc0")  # (tiles done: the only sum whose old value is used)
-    assert waited(body, count)
-    mark = max(i for i in range(count) if WRITE.match(body[i]))
+    ask = only(body, r"global_atomic_swap_x2 .* sc0")
+    assert waited(body, ask)
+    mark = max(i for i in range(ask) if WRITE.match(body[i]))
     assert body[mark].startswith("global_store_dwordx2") and body[mark].endswith("sc1")
     assert waited(body, mark)
     position = only(body, r"global_store_dword .* sc1")  # (the only 32-bit word stored through to memory)
     free = min(i for i in range(position + 1, len(body)) if WRITE.match(body[i]))
     assert body[free].startswith("global_store_dwordx2") and body[free].endswith("sc1")
     assert waited(body, free)
+    look = min(i for i in range(free + 1, len(body)) if body[i].startswith("global_load"))
+    assert any(WAIT.match(x) for x in body[free + 1:look])
