@@ -2095,7 +2095,11 @@ __global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, in
     // A tile whose entries take too long to sample would start more chains
     // than a map holds (~31 sources per segment with a new extreme on the
     // log-uniform mixes, and then too many runs): found out here, not after
-    // a build of 0.2 to 0.4 ms.
+    // a build of 0.2 to 0.4 ms.  Footprints that grow by single steps have one or
+    // two sources in each such segment, but chains that do not meet, so that
+    // they too come to too many runs: 70 tiles with a step in every fifth or in
+    // every segment, T = 64 MiB, 421 to 490 us for the resolve pass, and 440 to
+    // 635 where the sources were estimated first and the maps then tried.
     if (fresh_segs > TS_FRESH) {
         fail = TMF_SOURCES;
     } else if (bad) {
