@@ -273,7 +273,9 @@ SMP_API int sampler_last_counters(smp_sampler_t *s, uint64_t *out32);
  *   chain_grid : workgroups of the chain pass (0 = three times as many as
  *                the device holds at once)
  *   emit_grid  : workgroups of the emit pass (0 = as many as the device
- *                holds at once, for a batch of many traces a multiple)
+ *                holds at once, of the larger ones that a single trace of
+ *                4,096 segments or more takes fewer, for a batch of many
+ *                traces a multiple); at most one per 4 segments (8 for those)
  *   graphs     : 1 (default) = a run slot replays a launch sequence whose
  *                shape (trace count, segment, tile, block and line totals,
  *                grids, timing events) it launched before as a HIP graph,
@@ -288,7 +290,9 @@ SMP_API int sampler_last_counters(smp_sampler_t *s, uint64_t *out32);
  *                lookup per tile instead of a walk per tile (0 = the default,
  *                8; 0xFFFFFFFF = never)
  * sampler_set_tuning returns SMP_EINVAL for values out of range;
- * sampler_get_tuning reports the current ones with the defaults resolved. */
+ * sampler_get_tuning reports the current ones with the defaults resolved
+ * (emit_grid, whose default depends on the launch: what the last launch since
+ * sampler_set_tuning took, before any what a single short trace takes). */
 typedef struct {
     uint32_t chain_cap;
     uint32_t chain_grid;

@@ -80,8 +80,8 @@ def measure(sampler, workload, tuning, reps):
 
 
 def candidates(param, defaults):
-    """Values tried for one parameter; grids are factors of the device's
-    default (as many workgroups as it holds at once)."""
+    """Values tried for one parameter; grids are factors of the defaults that
+    the workload's launches took."""
     if param == "chain_cap":
         return list(CHAIN_CAPS)
     if param == "tile_map_tiles":
@@ -104,7 +104,6 @@ def tune(sampler, workload, size, *, cache_path=None, reps=3, key=None, log=None
         return {"key": key, "tuning": hit["tuning"], "ms": hit.get("ms"), "tried": hit.get("tried", {}),
                 "from_cache": True}
     sampler.set_tuning(**DEFAULT)
-    resolved = sampler.get_tuning()  # the device defaults of the grids
     best = dict(DEFAULT)
     tried = {}
 
@@ -113,6 +112,7 @@ def tune(sampler, workload, size, *, cache_path=None, reps=3, key=None, log=None
 
     best_ms = measure(sampler, workload, best, reps)
     tried[name(best)] = round(best_ms, 4)
+    resolved = sampler.get_tuning()  # the grids that the defaults gave this workload
     for param in ("tile_map_tiles", "chain_cap", "emit_grid", "chain_grid"):
         for v in candidates(param, resolved):
             cand = dict(best)

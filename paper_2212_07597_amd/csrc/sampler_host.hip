@@ -231,6 +231,7 @@ struct smp_sampler {
     uint64_t next_id = 1;
     uint64_t run_seq = 0;
     int grid_chain = 0, grid_emit = 0, grid_emit_wide = 0, grid_track = 0;
+    uint32_t last_emit_grid = 0;  // of the last launch
     double clock_khz = 0;           // rate of the device clock
     hipStream_t fetch_stream = nullptr;
     // Pinned host memory, one block for all slots each: their descriptor
@@ -299,6 +300,20 @@ bool wants_tile_maps(const smp_sampler* s, const TraceRec& t) {
     const uint64_t min_tiles = s->tuning.tile_map_tiles ? s->tuning.tile_map_tiles : TILE_MAP_TILES_DEFAULT;
     return t.lay.ntile >= min_tiles && t.lay.ntile > 1 &&
            sizeof(Tracked) * (t.n + 1) >= t.lay.ntile * TILE_MAP_ROOM;
+}
+
+// Workgroups of the emit pass, unless the caller sets them.  A batch's each take
+// one run of segments.  Up to four runs per trace, in whole rounds of the
+// workgroups that the GPU holds (1,280), let most of them see the lines of one
+// trace only, which their tables hold.  The emit pass with one round and by this
+// rule: 1,024 traces of 1e3-1e6 events 1.35 and 1.02 ms, 2,000 of 20,000 events
+// 664 and 425 us.  Below two rounds' worth of traces more workgroups only fill
+// and flush more tables: 2 traces of 1e7 events 177 us in one round and 214 in
+// two, 64 of 200,000 112 and 125, 400 of 50,000 161 and, with 1,600 workgroups,
+// 187.  The wide shape's workgroups are larger: as many as the GPU holds.
+uint64_t default_emit_grid(const smp_sampler* s, uint64_t traces, uint64_t nseg) {
+    if (emit_wide((int)traces, nseg)) return (uint64_t)s->grid_emit_wide;
+    return s->grid_emit * std::max<uint64_t>(1, 4 * traces / s->grid_emit);
 }
 
 #define HIPCHK(expr)                          \
@@ -599,19 +614,8 @@ int run(smp_sampler_t* s, int blocking) {
         }
         key.ev_mask = s->pass_events;
         key.chain_grid = s->tuning.chain_grid ? s->tuning.chain_grid : (uint64_t)s->grid_chain;
-        // A batch's emit workgroups each take one run of segments.  Up to four
-        // runs per trace, in whole rounds of the workgroups that the GPU holds
-        // (1,280), let most of them see the lines of one trace only, which
-        // their tables hold.  The emit pass with one round and by this rule:
-        // 1,024 traces of 1e3-1e6 events 1.35 and 1.02 ms, 2,000 of 20,000
-        // events 664 and 425 us.  Below two rounds' worth of traces more
-        // workgroups only fill and flush more tables: 2 traces of 1e7 events
-        // 177 us in one round and 214 in two, 64 of 200,000 112 and 125, 400
-        // of 50,000 161 and, with 1,600 workgroups, 187.
-        key.emit_grid = s->tuning.emit_grid ? s->tuning.emit_grid
-                                            : s->grid_emit * std::max<uint64_t>(1, 4 * cnt / s->grid_emit);
-        // (the wide shape's workgroups are larger: no more of them than the GPU holds)
-        if (emit_wide((int)cnt, key.seg)) key.emit_grid = std::min(key.emit_grid, (uint64_t)s->grid_emit_wide);
+        key.emit_grid = s->tuning.emit_grid ? s->tuning.emit_grid : default_emit_grid(s, cnt, key.seg);
+        s->last_emit_grid = (uint32_t)key.emit_grid;
         key.track_grid = (uint64_t)s->grid_track;
         // A free slot that launched this shape before (its graph or its
         // descriptors may be reused), else the free slot used longest ago,
@@ -893,6 +897,7 @@ int sampler_set_tuning(smp_sampler_t* s, const smp_tuning_t* t) {
         t->emit_grid > (1u << 20) || t->graphs > 1)
         return SMP_EINVAL;
     s->tuning = *t;
+    s->last_emit_grid = 0;
     return SMP_OK;
 }
 
@@ -900,7 +905,7 @@ int sampler_get_tuning(smp_sampler_t* s, smp_tuning_t* t) {
     if (!s || !t) return SMP_EINVAL;
     *t = s->tuning;
     if (!t->chain_grid) t->chain_grid = (uint32_t)s->grid_chain;
-    if (!t->emit_grid) t->emit_grid = (uint32_t)s->grid_emit;
+    if (!t->emit_grid) t->emit_grid = s->last_emit_grid ? s->last_emit_grid : (uint32_t)s->grid_emit;
     return SMP_OK;
 }
 

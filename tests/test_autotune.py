@@ -72,3 +72,20 @@ def test_unreadable_cache_is_empty(tmp_path):
     open(p, "w").write("{not json")
     assert autotune.load_cache(p) == {}
     assert autotune.load_cache(os.path.join(tmp_path, "missing.json")) == {}
+
+
+def test_candidates_come_from_the_workloads_own_default(tmp_path):
+    """A default grid that depends on what is launched is known once the
+    workload has run: factors of it are tried, and it itself not again."""
+
+    class Sized(FakeSampler):
+        DEFAULT_GRID = 100  # before any launch
+
+    s = Sized()
+
+    def workload():
+        s.DEFAULT_GRID = 1024
+
+    r = autotune.tune(s, workload, "t0-e13", cache_path=os.path.join(tmp_path, "t.json"), reps=1, key="k")
+    grids = {int(n.split("emit_grid=")[1]) for n in r["tried"]}
+    assert grids == {0, 512, 2048} and r["tuning"]["emit_grid"] == 2048

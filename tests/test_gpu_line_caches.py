@@ -59,3 +59,27 @@ def test_many_traces(sampler, count):
         cases.append((f"{count} traces, {i}", ev[i:i + n],
                       dict(threshold=tg.MiB // (1 << i % 4), num_lines=300, copy_threshold=100_003)))
     check(sampler, cases)
+
+
+def test_emit_grids(sampler):
+    """The default grid that a launch took is reported, written back it changes
+    nothing, and a larger one set by the caller is taken as it is."""
+    long = tg.mix(500, WIDE + 5, num_lines=60)
+    one = [("one long trace", long, dict(threshold=tg.MiB, num_lines=60, copy_threshold=tg.MiB))]
+    many = [(f"trace {i} of 1300", long[i:i + 700], one[0][2]) for i in range(1300)]
+    try:
+        sampler.set_tuning()
+        short = sampler.get_tuning()["emit_grid"]
+        for cases in (one, many):
+            sampler.set_tuning()
+            check(sampler, cases)
+            took = sampler.get_tuning()["emit_grid"]
+            assert took == short * 4 if cases is many else took < short
+            sampler.set_tuning(emit_grid=took)
+            check(sampler, cases)
+            assert sampler.get_tuning()["emit_grid"] == took
+        sampler.set_tuning(emit_grid=8 * short)
+        check(sampler, one)
+        assert sampler.get_tuning()["emit_grid"] == 8 * short
+    finally:
+        sampler.set_tuning()
