@@ -28,6 +28,13 @@ inline bool emit_wide(int ntraces, uint64_t nseg) { return ntraces == 1 && nseg 
 constexpr uint64_t TILE_MAP_BYTES = 32768;  // map area per tile (in the tracked-list area)
 constexpr uint64_t TILE_MAP_ROOM = 163840;  // with the scratch of a tile's blocks
 
+// |v - ref| >= T for values and T below 2^30 in magnitude: one unsigned compare
+// of v - ref + T - 1 with 2T - 1, formed modulo 2^32 (as a signed sum it would
+// pass 2^31 for T above 2/3 of the limit).
+constexpr bool beyond32(int32_t v, int32_t ref, int32_t T) {
+    return (uint32_t)v + (uint32_t)(T - 1) - (uint32_t)ref >= 2u * (uint32_t)T - 1u;
+}
+
 // Segments of block b (64 segments) of a tile of nval segments: none past the
 // trace's end.
 constexpr int block_segments(int nval, int b) {

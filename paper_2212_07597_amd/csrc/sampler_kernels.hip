@@ -1226,13 +1226,12 @@ __device__ __forceinline__ int first_samples(const int32_t* f, int32_t cgx, int3
     }
     g &= 63;
     const v4i32 a = *(const v4i32*)&f[8 * g], b = *(const v4i32*)&f[8 * g + 4];
-    const uint32_t span = (uint32_t)(2 * T - 1);
     int e = 7;
     v = b[3];
 #pragma unroll
     for (int i = 6; i >= 0; --i) {
         const int32_t y = i < 4 ? a[i & 3] : b[i & 3];
-        const bool c = (uint32_t)(y + (T - 1) - xr) >= span;
+        const bool c = beyond32(y, xr, T);
         e = c ? i : e;
         v = c ? y : v;
     }
@@ -2291,7 +2290,6 @@ template <bool CLAIM>
 __device__ __forceinline__ int follow_groups(BlockLds& B, int32_t gx, int32_t gn, int32_t T, int32_t& xr, int st,
                                              uint32_t tag, uint32_t id, bool one) {
     const int l = lane_id();
-    const uint32_t span = (uint32_t)(2 * T - 1);
     if (st >= SEG) return -1;
     int gfrom = st >> 3;
     uint64_t emask = (0xFFull << (st & 7)) & 0xFFull, gmask = ~0ull << gfrom;
@@ -2306,7 +2304,7 @@ __device__ __forceinline__ int follow_groups(BlockLds& B, int32_t gx, int32_t gn
             v = B.f[8 * g + (l & 7)];
             if (CLAIM) c = B.claim[8 * g + (l & 7)];
             asm volatile("" : "+v"(v), "+v"(c));  // (both reads in flight together)
-            m = ballot((uint32_t)(v + (T - 1) - xr) >= span) & (g == gfrom ? emask : 0xFFull);
+            m = ballot(beyond32(v, xr, T)) & (g == gfrom ? emask : 0xFFull);
             if (m) break;
             gm &= gm - 1;  // (the first group's crossings lie before st)
         }

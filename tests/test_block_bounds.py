@@ -1,6 +1,7 @@
-"""The kept prefixes that a tile's blocks load lie inside the trace's own
-sample area, for every number of segments: checked by the compiler, on the
-functions that the kernels use, over all blocks and segment masks' first bits."""
+"""Index and threshold arithmetic of the kernels, checked by the compiler on the
+functions that they use: the kept prefixes that a tile's blocks load lie inside
+the trace's own sample area, for every number of segments and first bit of a
+segment mask, and the 32-bit threshold test agrees with the 64-bit one."""
 import os
 import subprocess
 
@@ -43,10 +44,29 @@ static_assert(all_inside<8, 80>() && all_inside<80, 151>() && all_inside<500, 53
 """
 
 
+BEYOND = """
+#include "sampler_device.h"
+using namespace smp;
+
+// against the same comparison in 64 bits, at the ends of the range and around T (a signed overflow would not compile)
+constexpr bool same(int32_t T) {
+    const int32_t ends[] = {-(1 << 30) + 1, -(1 << 30) + 2, -T - 1, -T, -T + 1, -1, 0, 1, T - 1, T, (1 << 30) - 2, (1 << 30) - 1};
+    for (int32_t v : ends)
+        for (int32_t ref : ends) {
+            const int64_t d = (int64_t)v - ref;
+            if (beyond32(v, ref, T) != (d >= T || -d >= T)) return false;
+        }
+    return true;
+}
+static_assert(same(1) && same(2) && same(1 << 20) && same((1 << 30) / 3 * 2) && same((1 << 30) - 2) && same((1 << 30) - 1), "");
+"""
+
+
 @pytest.mark.skipif(not os.path.exists(_build.HIPCC), reason="no hipcc")
-def test_kept_prefixes_of_blocks(tmp_path):
-    src = tmp_path / "bounds.hip"
-    src.write_text(SOURCE)
+@pytest.mark.parametrize("text", [SOURCE, BEYOND], ids=["bounds", "threshold"])
+def test_arithmetic(tmp_path, text):
+    src = tmp_path / "check.hip"
+    src.write_text(text)
     flags = [f for f in _build.HIP_FLAGS if f not in ("-shared", "-fPIC")]
     r = subprocess.run([_build.HIPCC, *flags, "-fconstexpr-steps=100000000", "-I", os.path.join(_build.PKG, "csrc"), "-I",
                         os.path.join(_build.ROOT, "include"), "--cuda-device-only", "-fsyntax-only", str(src)],
