@@ -2901,6 +2901,7 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
         if (l == 0) s_bm[wv] = bm;
         __syncthreads();
         for (int w = 0; w < TWAVES; ++w) blocks = blocks && s_bm[w].ok != 0;
+        if (tid == 0) g_add((uint64_t*)&ctl[blocks ? 11 : 12], 1ull);
     }
     if (blocks) {
         if (wv == 0) {

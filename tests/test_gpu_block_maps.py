@@ -110,3 +110,30 @@ def test_workspace_without_room_to_spare(segments):
         compare(s.fetch_profile(tid), oracle.run(ev, threshold=2 * tg.MiB, num_lines=20), f"{segments} segments")
     finally:
         s.close()
+
+
+def counted(sampler, ev, T, label):
+    """(tiles resolved through block maps, tiles whose maps did not fit)."""
+    check(sampler, [(label, ev, dict(threshold=T, num_lines=50))])
+    return tuple(sampler.last_counters()[11:13])
+
+
+@pytest.mark.parametrize("n,maps", [(2 * BLK, 1), (2 * BLK + 1, 1), (3 * BLK - 1, 1), (3 * BLK, 1), (3 * BLK + 1, 1),
+                                    (5 * BLK + 31, 1), (TILE - 1, 1), (TILE, 1), (TILE + 8 * SEG, 2),
+                                    (TILE + 9 * SEG + 1, 2), (TILE + BLK - 1, 2), (TILE + BLK + 1, 2),
+                                    (2 * TILE + BLK + 300, 3)])
+def test_maps_are_taken(sampler, n, maps):
+    """Block and tile edges where the maps are what gives the result."""
+    ev = tg.mix(77, n, num_lines=50, copy_frac=0.05, timer_frac=0.01)
+    assert counted(sampler, ev, 3 * tg.MiB, f"maps at n{n}") == (maps, 0)
+
+
+def test_maps_that_are_not_taken(sampler):
+    """Short walks, chains that do not fit and thresholds past the 32-bit range."""
+    ev = tg.mix(77, 2 * TILE + BLK + 300, num_lines=50, copy_frac=0.05, timer_frac=0.01)
+    assert counted(sampler, ev[:BLK], 10 * tg.MiB, "one block, walked") == (0, 0)
+    assert counted(sampler, ev[:TILE], 30 * tg.MiB, "few stops, walked") == (0, 0)
+    taken, given_up = counted(sampler, ev, 30 * tg.MiB, "second tile's chains do not fit")
+    assert given_up >= 1
+    wide = tg.mix(79, 3 * BLK, num_lines=50, size_lo=1 << 20, size_hi=1 << 27)
+    assert counted(sampler, wide, 1 << 30, "threshold past the range") == (0, 0)

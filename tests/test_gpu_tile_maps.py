@@ -60,3 +60,19 @@ def test_many_tiles(sampler):
     assert c[5] >= 70 and c[6] >= 70
     c = check(sampler, ev[:8 * TILE], 400 * tg.MiB, "entries unsampled too long for a map")
     assert c[6] <= 8
+
+
+def test_maps_are_built(sampler):
+    """The cases above reach the paths that they are about: the 64-bit build
+    (all of these tiles need it) and the refusal before a build."""
+    ev = tg.mix(92, 2 * TILE + 5000, num_lines=40, size_lo=1 << 14, size_hi=1 << 25)
+    c = check(sampler, ev, 1 << 30, "T at 2^30, built", tiles=1)
+    assert c[5] >= 2 and c[6] == c[5]
+    ev = tg.mix(93, 2 * TILE + 5000, num_lines=40, size_lo=1 << 20, size_hi=1 << 28)
+    c = check(sampler, ev, 1 << 35, "steps past 2^30 in a segment, built", tiles=1)
+    assert c[5] >= 2 and c[6] == c[5]
+    ev = tg.mix(94, 8 * TILE, num_lines=40)
+    c = check(sampler, ev, 400 * tg.MiB, "refused")
+    assert c[5] == 0 and c[6] == 0 and c[8] == 8
+    c = check(sampler, ev, 2 * tg.MiB, "segments that move T or more")
+    assert c[5] == 0 and c[7] == 8
