@@ -310,8 +310,8 @@ int rate_launch(const smp_event_t* ev, uint64_t n, int64_t threshold, uint32_t n
     // Tiles of 8 segments up to RATE_BIG events, of 16 above: the large ones
     // halve the look-back's steps and the line caches that are flushed, the
     // small ones give short traces more workgroups.  Small against large: 1e5
-    // events 13.0 / 14.8 us, 4e5 18.1 / 17.7, 1e6 31.5 / 24.0 (64 lines) and
-    // 15.2 / 16.8 (10,000 lines), 3e6 66 / 41 and 35 / 31, 1e8 741 / 597.
+    // events 13.6 / 15.6 us, 4e5 14.2 / 16.4, 1e6 17.5 / 18.2, 3e6 36.5 / 33.5 (64
+    // lines; on 10,000 lines within 1.5 us of these), 1e8 719 / 604.
     const bool big = n > RATE_BIG;
     const uint64_t te = (uint64_t)SEG * (big ? 16 : 8);
     const uint64_t ntile = (n + te - 1) / te;
