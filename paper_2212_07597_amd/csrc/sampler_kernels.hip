@@ -2979,6 +2979,7 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
         int32_t pf[NW];
         int pf_lane = -1;
         auto walk = [&](int b, int e, int64_t x) -> int64_t {
+            x = readlane64(x, 0);  // (wave-uniform: scalar registers)
             for (int g0 = b & ~63; g0 < e && ok; g0 += 64) {
                 const int i = g0 + l;
                 const int64_t lo = m_lo[i], hi = m_hi[i], af = m_af[i], kf = m_kf[i];
