@@ -2901,7 +2901,6 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
         if (l == 0) s_bm[wv] = bm;
         __syncthreads();
         for (int w = 0; w < TWAVES; ++w) blocks = blocks && s_bm[w].ok != 0;
-        if (tid == 0) g_add((uint64_t*)&ctl[blocks ? 11 : 12], 1ull);
     }
     if (blocks) {
         if (wv == 0) {
@@ -3302,6 +3301,7 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
         if (p > 0) g_max(&D.scal->peak_F, (int64_t)p);
         if (q > 0) g_max(&D.scal->peak_S, (int64_t)q);
         if (c) g_add((uint64_t*)&ctl[4], c);
+        if (tried) g_add((uint64_t*)&ctl[blocks ? 11 : 12], 1ull);
     }
 }
 
