@@ -156,7 +156,8 @@ __device__ __forceinline__ uint64_t rate_div(uint64_t u, uint64_t T, uint64_t m,
 // Bound: HBM reads (24 bytes per event, once) and the look-back's latency (the
 // same kernel without its waits: 0.48 ms).  One call on 1e8 events at T = 10
 // MiB: 0.57 ms, 4.2 TB/s; as two passes over the records with a scan between
-// them it took 0.92 ms.  1e5 events: 17.5 -> 13 us (two launches, not four).
+// them it took 0.92 ms.  1e5 events: 17.5 -> 11 to
+// 13 us (two launches, not four).
 template <int WV>
 __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(4))) void k_rate(const uint8_t* __restrict__ ev, uint64_t n, uint64_t ntile,
                                                      uint32_t L, int64_t T, uint64_t m, uint64_t* hdr,

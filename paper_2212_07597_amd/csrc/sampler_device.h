@@ -22,8 +22,9 @@ constexpr int CHAIN_CAP_MAX = 64;        // chains the all-entry analysis can fo
 // Whether the emit pass takes its wide shape (large line tables shared by
 // eight waves): for one trace of 4,096 segments or more, one for each wave that
 // the GPU then holds.  With copies and timers on 100 and on 10,000 lines, wide
-// and narrow: 1 M events 42 and 45, 22 and 21 us; 2 M 73 and 81, 30 and 33;
-// 10 M 145 and 179, 106 and 128.
+// and narrow: 1 M events 26 and 27, 24 and 22 us; 2 M 38 and 43, 32 and 30; 10 M
+// 105 and 121, 107 and 101; 20 M on 100,000 lines 125 and 140, 10 M without
+// copies on 10,000 lines 74 and 82.
 inline bool emit_wide(int ntraces, uint64_t nseg) { return ntraces == 1 && nseg >= 4096; }
 constexpr uint64_t TILE_MAP_BYTES = 32768;  // map area per tile (in the tracked-list area)
 constexpr uint64_t TILE_MAP_ROOM = 163840;  // with the scratch of a tile's blocks

@@ -306,11 +306,11 @@ bool wants_tile_maps(const smp_sampler* s, const TraceRec& t) {
 // one run of segments.  Up to four runs per trace, in whole rounds of the
 // workgroups that the GPU holds (1,280), let most of them see the lines of one
 // trace only, which their tables hold.  The emit pass with one round and by this
-// rule: 1,024 traces of 1e3-1e6 events 1.35 and 1.02 ms, 2,000 of 20,000 events
-// 664 and 425 us.  Below two rounds' worth of traces more workgroups only fill
-// and flush more tables: 2 traces of 1e7 events 177 us in one round and 214 in
-// two, 64 of 200,000 112 and 125, 400 of 50,000 161 and, with 1,600 workgroups,
-// 187.  The wide shape's workgroups are larger: as many as the GPU holds.
+// rule: 1,024 traces of 1e3-1e6 events 1.35 and 1.01 ms, 2,000 of 20,000 events
+// with copies 379 and 332 us.  Below two rounds' worth of traces more workgroups
+// only fill and flush more tables (with copies): 2 traces of 1e7 events 204 us in
+// one round and 230 in two, 64 of 200,000 121 and 125, 400 of 50,000 170 and,
+// with 1,600 workgroups, 195.  The wide shape's workgroups are larger: as many as the GPU holds.
 uint64_t default_emit_grid(const smp_sampler* s, uint64_t traces, uint64_t nseg) {
     if (emit_wide((int)traces, nseg)) return (uint64_t)s->grid_emit_wide;
     return s->grid_emit * std::max<uint64_t>(1, 4 * traces / s->grid_emit);

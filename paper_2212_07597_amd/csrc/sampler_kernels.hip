@@ -3331,7 +3331,7 @@ __device__ __forceinline__ void load_head(const Desc& D, int64_t j, ChainHead& h
 
 // One wave per segment (grid-stride): follow the chain from the segment's
 // entry offset; record its samples, count, best growth sample and the Python
-// footprint at its last sample.  Copy and timer events are counted here.
+// footprint at its last sample.  (Copy and timer events are the emit pass's.)
 __global__ __launch_bounds__(BLOCK) void k_chain(const Desc* __restrict__ desc, int ntraces, uint64_t nseg_total,
                                                  uint64_t* ts) {
     stamp(ts);
@@ -3931,15 +3931,15 @@ __device__ __forceinline__ void emit_segment(const Desc* __restrict__ desc, cons
 // workgroups alike, so each of them meets every line, and the tables want to
 // be large.  Measured against four waves around one table of 128 slots with
 // 12 counters, five workgroups per CU: 500 M events with copies and timers on
-// 1 M lines 2.7-2.9 ms (4.1-4.3), 20 M on 100,000 lines 0.127 (0.25), 10 M
-// without them 0.069 (0.075), 100 M without 0.55-0.57 (0.54-0.57, bound by
+// 1 M lines 2.7-2.9 ms (4.1-4.3), 20 M on 100,000 lines 0.125 (0.25), 10 M
+// without them 0.074 (0.075), 100 M without 0.55-0.57 (0.54-0.57, bound by
 // the records).  16 waves, one workgroup per CU: 0.116 at 20 M, but
 // 0.56-0.58 at 100 M and 3.05 ms at 500 M.  Ten waves (five per SIMD): 0.142
 // and 0.62.
 // Narrow, five workgroups per CU: batches, whose workgroups meet the lines of
 // one or two traces, and short traces (see emit_wide).  1,024 traces of 1e3 to
-// 1e6 events 1.35 ms (1.44); 16 traces of 2 M events with
-// copies on 100 lines 0.24 (0.26), the wide shape 0.27; 2 of 10 M 0.20 (0.33).
+// 1e6 events 1.35 ms (1.44) in one round of workgroups; 16 traces of 2 M events
+// with copies on 100 lines 0.26, the wide shape 0.28; 2 of 10 M 0.18 and 0.19.
 // Four workgroups per CU with 512 slots for samples: 1.2 ms for the 1,024
 // traces, but 0.28-0.33 for the 16.
 struct EmitWide { static constexpr int WAVES = 8, PER_SIMD = 4, SAMPLES = 512, AUX = 1024; };
