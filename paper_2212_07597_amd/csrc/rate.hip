@@ -213,14 +213,16 @@ __global__ __launch_bounds__(64 * WV) __attribute__((amdgpu_waves_per_eu(4))) vo
         if (l == 0) s_sum[wv] = mine;
         if (badm && l == 0) g_or(hdr + RH_FLAGS, RF_BAD);
         __syncthreads();
-        // (16 waves of 2^61 would wrap: the sum stops at VOL_LIMIT, which the
-        // tile's own look-back flags)
-        before = agg = 0;
+        // (each eight waves' sum stays below 2^64; 16 would wrap, and one that
+        // reaches VOL_LIMIT stands for the tile's, which its look-back flags.  A
+        // limit after every wave's addition cost 4 % of the call)
+        uint64_t half[2] = {0, 0};
+#pragma unroll
         for (int w = 0; w < WV; ++w) {
-            if (w == wv) before = agg;
-            agg += s_sum[w];
-            agg = agg < VOL_LIMIT ? agg : VOL_LIMIT;
+            if (w == wv) before = half[0] + half[1];
+            half[w >> 3] += s_sum[w];
         }
+        agg = ((half[0] | half[1]) >> 62) ? VOL_LIMIT : half[0] + half[1];
         if (tid == 0) st_status(st + t, (agg < VOL_MASK ? agg : VOL_MASK) | (t == 0 ? 2ull : 1ull) << 62);
     };
     uint64_t t = take_ticket();
