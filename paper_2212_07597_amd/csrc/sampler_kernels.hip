@@ -2214,10 +2214,12 @@ __global__ __launch_bounds__(TILE) void k_tmap(const Desc* __restrict__ desc, in
 // traces of 1e3-1e6 events at T = 256 KiB / 1 MiB / 10 MiB 1.12 -> 0.28 ms; a
 // trace of 777,777 events at T = 3 MiB (three tiles) 1.53 -> 0.15 ms; one of
 // 1.2e7 events at T = 10 MiB 9.5 -> 0.2 ms.  (Prefixes two segments ahead
-// instead of one: 25 spilled registers and 0.16 / 0.29 ms.) 
+// instead of one: 25 spilled registers and 0.16 / 0.29 ms.)
 constexpr int BM_SRC = 512;   // sources per block
 constexpr int BM_OPEN = 14;   // ~31 sources per segment on the log-uniform mixes while entries are left
-//
+constexpr int BM_MIN_SIM = 8; // SIM segments from which a waiting tile builds its maps
+constexpr int BM_PAR = 4;     // chains that stop in a segment from which they are searched side by side
+
 // Whether a tile takes them.  One that has to wait for its entry builds them
 // meanwhile (from BM_MIN_SIM SIM segments on: 700 segments, the last 188 of them
 // a tile of their own, T = 10 MiB, 140 us, and 242 with the second tile walked).
@@ -2237,8 +2239,6 @@ __device__ __forceinline__ int block_cost(int many, int after) { return 200 + 31
 __device__ __forceinline__ bool block_maps_pay(bool sparse, int stops, int slowest) {
     return (sparse ? 17 : 25) * stops / 256 > slowest;
 }
-constexpr int BM_MIN_SIM = 8;
-constexpr int BM_PAR = 4;     // chains that stop in a segment from which they are searched side by side
 
 struct alignas(16) BlockLds {
     int32_t f[SEG];          // the current SIM segment's prefixes
@@ -2764,7 +2764,8 @@ __global__ __launch_bounds__(TILE) __attribute__((amdgpu_waves_per_eu(4))) void 
     const int nval = (int)((ns - k * TILE) < TILE ? (ns - k * TILE) : TILE);  // valid lanes
     const StatusView ts{D.tstat, (int64_t)D.ntile};
     if (D.tmap && tid == 0) D.blk[k] = 0;  // (the mark of a tile map)
-    // (a tile map may have published the previous tile's exit)
+    // (published by a tile map or by a tile that is done already: decides how this
+    // tile is followed, not what comes out)
     if (k > 0 && tid == 0) s_known = wstate(ld_status(ts.at(W_XF, k - 1))) != 0;
     const SMP_GLOBAL int64_t* sp = gp(D.seg) + (valid ? j : 0);
     int64_t af = 0, ap = 0, ac = 0, kf = 0, lo = 0, hi = 0, mxf = 0, mnf = 0;
