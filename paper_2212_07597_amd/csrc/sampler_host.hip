@@ -795,17 +795,20 @@ int fetch_profile(smp_sampler_t* s, uint64_t trace_id, smp_profile_sizes_t* size
         if (out->leak) memcpy(out->leak, per_line + (t.lay.leak - t.lay.hist), 8 * 4 * L);
         if (out->gates) memcpy(out->gates, per_line + (t.lay.gates - t.lay.hist), 2 * L);
     } else {
+        // (whatever fails, no copy is left under way into the caller's arrays)
+        hipError_t e = hipSuccess;
         auto copy = [&](void* dst, uint64_t off, uint64_t bytes) {
-            return !dst || !bytes
-                       ? hipSuccess
-                       : hipMemcpyAsync(dst, base + off, bytes, hipMemcpyDeviceToHost, s->fetch_stream);
+            if (dst && bytes && e == hipSuccess)
+                e = hipMemcpyAsync(dst, base + off, bytes, hipMemcpyDeviceToHost, s->fetch_stream);
         };
-        HIPCHK(copy(out->samples, t.lay.samples, bs));
-        HIPCHK(copy(out->tracked, t.lay.tracked, bt));
-        HIPCHK(copy(out->hist, t.lay.hist, 8 * H_COUNT * L));
-        HIPCHK(copy(out->leak, t.lay.leak, 8 * 4 * L));
-        HIPCHK(copy(out->gates, t.lay.gates, 2 * L));
-        HIPCHK(hipStreamSynchronize(s->fetch_stream));
+        copy(out->samples, t.lay.samples, bs);
+        copy(out->tracked, t.lay.tracked, bt);
+        copy(out->hist, t.lay.hist, 8 * H_COUNT * L);
+        copy(out->leak, t.lay.leak, 8 * 4 * L);
+        copy(out->gates, t.lay.gates, 2 * L);
+        const hipError_t done = hipStreamSynchronize(s->fetch_stream);
+        HIPCHK(e);
+        HIPCHK(done);
     }
     out->final_F = sc.final_F;
     out->peak_F = sc.peak_F;
